@@ -271,7 +271,12 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *                        partner frequency is a dense product of a block of
  *                        phase rows with a block of weighted phases, evaluated
  *                        with 16x16x4 MFMAs (FP32: v_mfma_f32_16x16x4_f32 with
- *                        two-sum flushes; FP64: v_mfma_f64_16x16x4_f64).  Same
+ *                        two-sum flushes; FP64: v_mfma_f64_16x16x4_f64).  FP32
+ *                        plans with the default tile shape, unit phases (no
+ *                        line_r, wind or product factors) and n_kappa >= 32 take
+ *                        each FP32 product as three FP16 products of split
+ *                        phases with FP32 sums, as accurate as the FP32 form
+ *                        (v_mfma_f32_16x16x32_f16).  Same
  *                        result up to rounding.  Output rows go in groups of
  *                        32 kappa rows: grids with few rows (a 1-D process has
  *                        one) leave most of each product idle and are better
@@ -294,7 +299,8 @@ srm3_status srm3_plan_set_algorithm(srm3_plan_t plan, int32_t algorithm, void *h
  * srm3_generate / srm3_coefficients on this plan: each wave owns `rows` kappa
  * rows x `cols` frequency columns of outputs (srm3_mfma_shape tells them for a
  * precision): shape 0 (the default) 32 x 32, shape 1 32 x 16, shape 2
- * 16 x 32, in FP32 and FP64.  The smaller tiles leave more waves resident per
+ * 16 x 32, in FP32 and FP64 (FP32 with shape 0 uses the split-FP16 form where
+ * SRM3_ALGO_MFMA allows it).  The smaller tiles leave more waves resident per
  * SIMD and fit grids with few rows or columns better; every shape sums the same
  * pair terms, so results agree up to rounding.  Uneven batches created with
  * SRM3_BATCH_AUTOTUNE pick their shape by timing.  Errors: SRM3_E_INVALID (NULL

@@ -106,6 +106,14 @@ srm3_status refresh_amp_table(srm3_plan_t p, hipStream_t st)
     return SRM3_OK;
 }
 
+// The matrix-core form with the default tile shape (32 x 32 lines per wave on
+// the FP32 path) takes its products in split FP16 where the phases are unit.
+bool split_plan(srm3_plan_t p, int shape)
+{
+    return p->algo == SRM3_ALGO_MFMA && shape == 0 && !p->gaussian && !p->hashed &&
+           split_supported(p->g, p->precision, p->lr.p != nullptr);
+}
+
 double max_sigma(double max_sig, double cap, double scale)
 {
     const double s = scale * max_sig;
@@ -202,6 +210,8 @@ srm3_status event_pair(srm3_plan_t p, int kernel, hipStream_t st, bool begin)
 // The pair-sum algorithms that go through a DFT along kappa (own workspace and tables).
 bool kfft_family(int algo) { return algo == SRM3_ALGO_KAPPA_FFT || algo == SRM3_ALGO_FFT2D; }
 
+bool split_form(srm3_plan_t p) { return split_plan(p, p->mfma_shape); }
+
 srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
 {
     if (batch > p->ws_batch) {
@@ -244,7 +254,10 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     if ((s = event_pair(p, 0, st, true))) return s;
     Workspace wp = ws;
     if (p->gaussian || p->hashed || kfft_family(p->algo)) wp.zcol = nullptr;   // no a operand planes needed
-    hipError_t e = launch_phases(p->g, p->precision, seeds, nullptr, batch, wp, static_cast<const double *>(p->lr.p), st);
+    const bool split = split_form(p);
+    hipError_t e = split ? launch_phases_split(p->g, seeds, nullptr, batch, wp, st)
+                         : launch_phases(p->g, p->precision, seeds, nullptr, batch, wp,
+                                         static_cast<const double *>(p->lr.p), st);
     if (e != hipSuccess) return dev_err(e, "phase kernel");
     if ((s = event_pair(p, 0, st, false))) return s;
     if (p->gaussian) return SRM3_OK;   // zero bicoherence: the pair sums are not used
@@ -255,6 +268,9 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     } else if (kfft_family(p->algo)) {
         e = launch_kfft_pairsum(p->precision, p->g, p->kg, plan_ktab(p), batch, ws, kw, st);
         if (e != hipSuccess) return dev_err(e, "kappa-FFT pair-sum kernels");
+    } else if (split) {
+        e = launch_pairsum_split(p->g, p->wtab.p, batch, ws, st);
+        if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
     } else if (p->algo == SRM3_ALGO_MFMA) {
         e = launch_pairsum_mfma(p->g, p->precision, p->mfma_shape, p->wtab.p, batch, ws, st);
         if (e != hipSuccess) return dev_err(e, "matrix-core pair-sum kernel");
@@ -541,6 +557,7 @@ srm3_status srm3_plan(const srm3_grid *grid, const srm3_spectrum *spectrum, cons
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) return dev_err(e, "hipGetDevice");
     e = prepare_transforms(precision);
+    if (e == hipSuccess) e = prepare_split();
     if (e != hipSuccess) return dev_err(e, "hipFuncSetAttribute");
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1063,6 +1080,7 @@ struct srm3_batch_s {
         Geometry g;                    // with the batch's R
         size_t ws_off = 0;
         int first = 0;                 // offset of the group in the device arrays
+        bool split = false;            // mode 0 in split FP16: its items are in the split launch
         int mode = 0;                  // 0: items of the persistent launch; 1: the plan's kappa-DFT
                                        // pair sum over the group; 2: zero bicoherence, no pair sum
         size_t kws_off = 0;            // kappa-DFT workspace of the group (mode 1)
@@ -1074,7 +1092,10 @@ struct srm3_batch_s {
     int blocks_per_cu = 2;
     int n_cu = 256;
     DevBuf ws, seeds, scales, sptr, outs, preq, pitem, qbegin, qnext;
-    int n_items = 0;
+    int n_items = 0, plain_items = 0;  // all work items; those of the persistent launch
+    DevBuf split_items, split_ctr;     // work list of the split-FP16 pair sum and its counters
+    SplitItems split_n;
+    int split_tiles = 0;
     uint64_t *seeds_host = nullptr;    // pinned staging
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
@@ -1136,6 +1157,7 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
     for (auto &gr : b->groups) {
         gr.g = gr.plan->g;
         gr.mode = gr.plan->gaussian ? 2 : (kfft_family(gr.plan->algo) ? 1 : 0);
+        gr.split = gr.mode == 0 && split_plan(gr.plan, b->mfma_shape);
         if (gr.mode == 0) {
             gr.g.R = rows_for(gr.g.nk, b->precision, R);
             gr.g.nkp = ((gr.g.nk + gr.g.R - 1) / gr.g.R) * gr.g.R;
@@ -1167,11 +1189,12 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
     std::vector<std::vector<It>> per_req(b->n);
     std::vector<double> req_cost(b->n, 0.0);
     const size_t e = b->precision == SRM3_FP64 ? 8 : 4;
+    SplitList split;
     for (auto &gr : b->groups) {
         const Workspace ws = carve_workspace(gr.g, b->precision, static_cast<int>(gr.members.size()),
                                              static_cast<char *>(b->ws.p) + gr.ws_off);
         const size_t lines = static_cast<size_t>(gr.g.nk) * gr.g.nc;
-        const size_t plane3 = a_slots(b->precision) * gr.g.ncw * gr.g.nkp;
+        const size_t a_bytes = gr.split ? split_operand_bytes(gr.g) : a_slots(b->precision) * gr.g.ncw * gr.g.nkp * e;
         const int mr = mfma_rows_per_group(b->precision, b->mfma_shape);
         const int mc = mfma_cols_per_group(b->precision, b->mfma_shape);
         const int nrb = b->mfma ? (gr.g.nk + mr - 1) / mr : gr.g.nkp / gr.g.R;
@@ -1181,8 +1204,12 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
         for (size_t slot = 0; slot < gr.members.size(); ++slot) {
             const int d = gr.first + static_cast<int>(slot);
             fill_persistent_req(reqs.data() + rb * d, gr.g, static_cast<char *>(ws.zrow) + slot * lines * 2 * e,
-                                static_cast<char *>(ws.zcol) + slot * plane3 * e,
+                                static_cast<char *>(ws.zcol) + slot * a_bytes,
                                 static_cast<char *>(ws.tsum) + slot * lines * 2 * e, gr.plan->wtab.p);
+            if (gr.split) {
+                split.add(d, gr.g);
+                continue;
+            }
             for (int kb = nrb - 1; kb >= 0; --kb)
                 for (int cg = 0; cg < ncg; ++cg) {
                     const double c = b->mfma ? mfma_item_cost_impl(gr.g, kb, cg, b->precision, b->mfma_shape)
@@ -1217,8 +1244,16 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
     while (q <= kXcds) qbegin[q++] = static_cast<int>(all.size());
     std::vector<unsigned char> items(ib * std::max<size_t>(1, all.size()));
     for (size_t i = 0; i < all.size(); ++i) fill_persistent_item(items.data() + ib * i, all[i].req, all[i].kb, all[i].cg);
-    b->n_items = static_cast<int>(all.size());
+    const std::vector<unsigned char> sitems = split.items(&b->split_n);
+    b->split_tiles = split.tiles();
+    b->n_items = static_cast<int>(all.size()) + b->split_n.begin[kSplitShapes];
+    b->plain_items = static_cast<int>(all.size());
     srm3_status s;
+    if (b->split_tiles > 0) {
+        if ((s = upload_bytes(b->split_items, sitems.data(), sitems.size(), st))) return s;
+        const hipError_t er = b->split_ctr.alloc(split_counter_words(b->split_tiles) * sizeof(unsigned));
+        if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
+    }
     if ((s = upload_bytes(b->preq, reqs.data(), reqs.size(), st))) return s;
     if ((s = upload_bytes(b->pitem, items.data(), items.size(), st))) return s;
     if ((s = upload_bytes(b->qbegin, qbegin.data(), qbegin.size() * sizeof(int), st))) return s;
@@ -1236,9 +1271,11 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
         Workspace ws = carve_workspace(gr.g, b->precision, static_cast<int>(gr.members.size()),
                                        static_cast<char *>(b->ws.p) + gr.ws_off);
         if (gr.mode != 0) ws.zcol = nullptr;   // no a operand planes needed
-        hipError_t e = launch_phases(gr.g, b->precision, nullptr, static_cast<const uint64_t *>(b->seeds.p) + gr.first,
-                                     static_cast<int>(gr.members.size()), ws,
-                                     static_cast<const double *>(gr.plan->lr.p), st);
+        const uint64_t *seeds = static_cast<const uint64_t *>(b->seeds.p) + gr.first;
+        const int nb = static_cast<int>(gr.members.size());
+        hipError_t e = gr.split ? launch_phases_split(gr.g, nullptr, seeds, nb, ws, st)
+                                : launch_phases(gr.g, b->precision, nullptr, seeds, nb, ws,
+                                                static_cast<const double *>(gr.plan->lr.p), st);
         if (e != hipSuccess) return dev_err(e, "phase kernel");
     }
     if (time_pairsum) (void)hipEventRecord(b->ev_a, st);
@@ -1252,7 +1289,12 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
         e = launch_kfft_pairsum(b->precision, gr.g, gr.plan->kg, plan_ktab(gr.plan), nb, ws, kw, st);
         if (e != hipSuccess) return dev_err(e, "kappa-DFT pair-sum kernels");
     }
-    if (b->n_items > 0) {
+    if (b->split_tiles > 0) {
+        e = launch_pairsum_split_items(b->preq.p, b->split_items.p, b->split_n, b->split_tiles,
+                                       static_cast<unsigned *>(b->split_ctr.p), st);
+        if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
+    }
+    if (b->plain_items > 0) {
         e = launch_pairsum_persistent(b->precision, b->R, b->preq.p, b->pitem.p,
                                       static_cast<const int *>(b->qbegin.p), static_cast<int *>(b->qnext.p),
                                       b->n_cu * b->blocks_per_cu, st, b->mfma, b->mfma_shape);

@@ -151,6 +151,51 @@ constexpr int kMfmaShapes = 3;
 MfmaShape mfma_shape(int precision, int shape);
 hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, const void *wtab, int batch,
                                const Workspace &ws, hipStream_t st);
+// The FP32 direct form on the FP16 matrix cores with split phases (see
+// srm3_split.hip): its phase kernel (the a operand region of the workspace
+// then holds the FP16 parts) and pair sum, for unit phases (no line factors).
+constexpr int kSplitMinRows = 32;   // (the FP16 parts fit the a operand region from 30 rows on)
+bool split_supported(const Geometry &g, int precision, bool line_factors);
+hipError_t launch_phases_split(const Geometry &g, const uint64_t *seeds, const uint64_t *seeds_dev, int batch,
+                               const Workspace &ws, hipStream_t st);
+hipError_t launch_pairsum_split(const Geometry &g, const void *wtab, int batch, const Workspace &ws, hipStream_t st);
+// The same over a work list: items (request, row tile, column tile, chunk of
+// partner columns) grouped by tile shape (shape i from begin[i] to
+// begin[i + 1]), the chunks of a tile in ascending order; `counters` holds
+// kSplitShapes + tiles words (zeroed here).
+constexpr int kSplitShapes = 3;
+struct SplitItems {
+    int begin[kSplitShapes + 1] = {0, 0, 0, 0};
+};
+hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const SplitItems &n, int tiles,
+                                      unsigned *counters, hipStream_t st);
+int split_shape(const Geometry &g);   // 0: 256 x 32 lines, 1: 128 x 64, 2: 64 x 128
+size_t split_operand_bytes(const Geometry &g);   // a operand of one realization
+inline size_t split_counter_words(int tiles) { return kSplitShapes + static_cast<size_t>(tiles); }
+// A work list under construction: whole tiles of requests, in the order added.
+struct SplitTile {
+    int req, rs, cg, chunks;
+    double cost;
+};
+// Tiles of one request, heaviest first (cost: pair terms).
+std::vector<SplitTile> split_tiles(const Geometry &g, int req);
+class SplitList {
+public:
+    void add(int req, const Geometry &g);                       // every tile of a request
+    void add(int shape, const std::vector<SplitTile> &tiles);   // some tiles of one request
+    int tiles() const { return n_tiles_; }
+    // Items by shape, requests by descending cost, each chunk by chunk.
+    std::vector<unsigned char> items(SplitItems *n);
+
+private:
+    struct Run {
+        std::vector<SplitTile> tiles;
+        double cost;
+    };
+    std::vector<Run> runs_[kSplitShapes];
+    int n_tiles_ = 0;
+};
+hipError_t prepare_split();
 // Bispectrum generated per pair inside the kernel (hashed b^2 and beta).  With
 // ws == nullptr it writes the per-line raw sums sum b^2_raw to sig (FP64).
 hipError_t launch_pairsum_hash(const Geometry &g, int precision, uint64_t key, double scale, int batch,
@@ -333,5 +378,8 @@ struct srm3_plan_s {
 
 namespace srm3 {
 AmpRef plan_amp(srm3_plan_t p);
+// Whether the plan's direct-form pair sum runs in split FP16 (shape: the
+// matrix-core tile shape in use).
+bool split_plan(srm3_plan_t p, int shape);
 KfftTables plan_ktab(srm3_plan_t p);
 }  // namespace srm3

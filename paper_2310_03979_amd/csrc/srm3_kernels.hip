@@ -9,6 +9,7 @@
 #include <cstring>
 #include <string>
 
+#include "srm3_device.hpp"
 #include "srm3_internal.hpp"
 
 namespace srm3 {
@@ -62,46 +63,13 @@ __device__ __forceinline__ cptr<T> as_const(const T *p)
     return (cptr<T>)p;
 }
 
-// A pointer that every lane of the wave holds, taken from the first lane so
-// that address arithmetic on it stays scalar.
-template <typename T>
-__device__ __forceinline__ T *uniform_ptr(T *p)
-{
-    const unsigned long long v = reinterpret_cast<unsigned long long>(p);
-    const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
-    const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
-    return reinterpret_cast<T *>((static_cast<unsigned long long>(hi) << 32) | lo);
-}
-
-// Device memory in the global address space: loads through such a pointer are
-// global (not flat) loads also where the pointer itself was read from memory.
-#if defined(__HIP_DEVICE_COMPILE__)
-template <typename T>
-using gptr = const __attribute__((address_space(1))) T *;
-#else
-template <typename T>
-using gptr = const T *;
-#endif
-
 template <typename T>
 __device__ __forceinline__ gptr<T> as_global(const T *p)
 {
     return (gptr<T>)p;
 }
 
-// The b operand is read with buffer loads: the realization's phase rows form
-// one buffer resource (uniform), the lane's column is a fixed per-lane byte
-// offset and the row a uniform byte offset, so stepping along kappa costs no
-// vector address arithmetic (and reads past the buffer return zero).
 #if defined(__HIP_DEVICE_COMPILE__)
-using brsrc = __amdgpu_buffer_rsrc_t;
-__device__ __forceinline__ brsrc make_brsrc(const void *p, unsigned bytes)
-{
-    // the resource lives in scalar registers (the base is wave-uniform);
-    // word 3 of a gfx9 raw buffer resource: 32-bit data format, no swizzle
-    return __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(const_cast<void *>(p)), static_cast<short>(0),
-                                             static_cast<int>(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000);
-}
 // (The loaded vector is copied out whole: extracting its lanes one by one has
 // been folded by the compiler into a single-dword load.)
 __device__ __forceinline__ float2 bload(brsrc r, unsigned voff, unsigned soff, float)
@@ -133,10 +101,6 @@ __device__ __forceinline__ double bload64(brsrc r, unsigned voff, unsigned soff)
     return d;
 }
 #else
-struct brsrc {
-    const void *p;
-};
-__device__ inline brsrc make_brsrc(const void *p, unsigned) { return brsrc{p}; }
 __device__ inline float2 bload(brsrc, unsigned, unsigned, float) { return float2{}; }
 __device__ inline double2 bload(brsrc, unsigned, unsigned, double) { return double2{}; }
 __device__ inline float bload32(brsrc, unsigned, unsigned) { return 0.0f; }
@@ -158,63 +122,6 @@ template <> struct ALayout<double> {
     static constexpr int NS = 4;
     __device__ static long plane(const Geometry &) { return 1; }
 };
-
-// ---------------------------------------------------------------------------
-// Phase factor e^{i phi} of a 32-bit fixed-point phase u (phi = 2 pi u / 2^32)
-// in FP64, shared by every kernel that draws phases: the top 8 bits select
-// e^{2 pi i (u >> 24) / 256} from a 256-entry table (FP64 sincospi, built in
-// LDS by each block), the low 24 bits give theta = 2 pi (u mod 2^24) / 2^32 <
-// 2 pi / 256, whose cosine and sine come from their Taylor series through
-// theta^6 and theta^7 (the next terms are below 1e-17), and the two factors
-// are multiplied: a few ulp of FP64, for a fraction of a sincos.  The
-// arithmetic is written out in fma() calls so that no call site can contract
-// it differently (phases drawn by different kernels agree bitwise).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void phase_table_fill(double2 *tab)
-{
-    for (int m = threadIdx.x; m < 256; m += blockDim.x) {
-        double sn, cs;
-        sincospi(static_cast<double>(m) * (1.0 / 128.0), &sn, &cs);
-        tab[m] = make_double2(cs, sn);
-    }
-}
-
-__device__ __forceinline__ void phase_cs(uint32_t u, const double2 *tab, double &c, double &s)
-{
-    const double2 t = tab[u >> 24];
-    const double th = static_cast<double>(u & 0xFFFFFFu) * 1.4629180792671596e-09;   // 2 pi / 2^32
-    const double t2 = th * th;
-    const double ct = fma(t2, fma(t2, fma(t2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
-    const double st = th * fma(t2, fma(t2, fma(t2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
-    // explicit fused products: every kernel that inlines this rounds alike
-    c = fma(t.x, ct, -(t.y * st));
-    s = fma(t.y, ct, t.x * st);
-}
-
-// Phase words.  One Philox4x32-10 call (key = the realization's seed) serves
-// the four consecutive frequencies k_omega = 4 q .. 4 q + 3 of row k_kappa:
-// counter (k_kappa, q, 0, 0), word k_omega - 4 q.  q = floor(k_omega / 4).
-// ---------------------------------------------------------------------------
-__host__ __device__ inline int floor_div4(int kw) { return (kw >= 0 ? kw : kw - 3) / 4; }
-
-__device__ __forceinline__ void phase_words(int kk, int q, uint64_t seed, uint32_t (&w)[4])
-{
-    philox_words4(static_cast<uint32_t>(kk), static_cast<uint32_t>(q), 0u, 0u, seed, w);
-}
-
-// Phase factor of a line with its per-line complex factor rho_k (if any).
-__device__ __forceinline__ void phase_line(uint32_t u, const double2 *ptab, const double *__restrict__ lr, long l,
-                                           double &co, double &s)
-{
-    phase_cs(u, ptab, co, s);
-    if (lr) {
-        // per-line complex bicoherence factor rho_k carried by the phase factor
-        const double xr = lr[2 * l], xi = lr[2 * l + 1];
-        const double cr = fma(co, xr, -(s * xi)), ci = fma(co, xi, s * xr);   // fused as in phase_cs
-        co = cr;
-        s = ci;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Phases with the a operand.  A block covers a tile of 64 frequencies (16
@@ -970,18 +877,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
 // A block first drains the queue of its own XCD (block id mod 8), then steals
 // from the others.  The computation of an item does not depend on which block
 // runs it, so results are bitwise those of the direct launch.
-struct PReq {
-    Geometry g;
-    const void *zrow;
-    const void *zcol;
-    void *tsum;
-    const void *wtab;
-    int n_ctiles;
-    int pad;
-};
-struct PItem {
-    int req, kb, cg, pad;
-};
 struct PersistArgs {
     const PReq *reqs;
     const PItem *items;

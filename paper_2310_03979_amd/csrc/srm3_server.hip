@@ -43,6 +43,7 @@ struct SlotHeader {
 struct Item {
     int kb, cg;
     double cost;
+    int chunks = 1;   // work items of the launch that it stands for (tiles of the split launch)
 };
 
 struct SReq {
@@ -58,6 +59,7 @@ struct SReq {
                                     // pair sum, run at admission; 2: zero bicoherence, no pair sum
     size_t kfft_off = 0;            // arena offset of the kappa-DFT workspace (mode 1)
     std::vector<Item> items;        // heaviest first
+    bool split = false;             // pair sum in split FP16: items are tiles of the split launch
     size_t cursor = 0;
     double left = 0.0;              // cost of the items not yet issued
     hipEvent_t done = nullptr;
@@ -125,7 +127,7 @@ struct srm3_server_s {
     // staging: headers | qbegin | preq | items
     size_t off_hdr = 0, off_q = 0, off_req = 0, off_items = 0, stage_bytes = 0;
     int max_items = 0;
-    DevBuf dev_stage[2], qnext[2];
+    DevBuf dev_stage[2], qnext[2], split_ctr[2];
     unsigned char *pinned[2] = {nullptr, nullptr};
     hipEvent_t copied[2] = {nullptr, nullptr};
     bool copy_pending[2] = {false, false};
@@ -234,10 +236,11 @@ srm3_status srm3_server_create(const srm3_server_config *cfg, void *hip_stream, 
     s->off_q = align256(sizeof(SlotHeader) * na);
     s->off_req = s->off_q + align256(sizeof(int) * (kXcds + 1));
     s->off_items = s->off_req + align256(persistent_req_bytes() * na);
-    s->stage_bytes = s->off_items + align256(persistent_item_bytes() * s->max_items);
+    s->stage_bytes = s->off_items + align256(persistent_item_bytes() * (s->max_items + 1));
     for (int i = 0; i < 2; ++i) {
         if ((e = s->dev_stage[i].alloc(s->stage_bytes)) != hipSuccess ||
-            (e = s->qnext[i].alloc(kXcds * sizeof(int))) != hipSuccess)
+            (e = s->qnext[i].alloc(kXcds * sizeof(int))) != hipSuccess ||
+            (e = s->split_ctr[i].alloc(split_counter_words(s->max_items) * sizeof(unsigned))) != hipSuccess)
             return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
         if ((e = hipStreamCreateWithFlags(&s->lane[i], hipStreamNonBlocking)) != hipSuccess)
             return dev_err(e, "hipStreamCreate");
@@ -306,7 +309,12 @@ srm3_status srm3_server_submit(srm3_server_t s, const srm3_request *req, const s
     }
     if (q->bytes > s->arena.size)
         return fail(SRM3_E_NOMEM, "request needs %zu bytes, more than the server's budget %zu", q->bytes, s->arena.size);
-    if (q->mode == 0) {
+    q->split = q->mode == 0 && split_plan(r.plan, s->mfma_shape);
+    if (q->split) {
+        for (const SplitTile &t : split_tiles(q->g, 0))
+            q->items.push_back({t.rs, t.cg, t.cost / (64.0 * waves_per_block() * s->R), t.chunks});
+        for (const Item &it : q->items) q->left += it.cost;
+    } else if (q->mode == 0) {
         const int mr = mfma_rows_per_group(s->cfg.precision, s->mfma_shape);
         const int mc = mfma_cols_per_group(s->cfg.precision, s->mfma_shape);
         const int nrb = s->mfma ? (q->g.nk + mr - 1) / mr : q->g.nkp / q->g.R;
@@ -375,7 +383,9 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         const int min_items = 2 * s->n_cu * s->blocks_per_cu;
         double spent = 0.0;
         int n_items = 0;
-        auto full = [&]() { return (spent >= budget && n_items >= min_items) || n_items >= s->max_items; };
+        // (room: the next of a request's items still fits the step's list)
+        auto full = [&]() { return spent >= budget && n_items >= min_items; };
+        auto room = [&](const SReq *q) { return n_items + q->items[q->cursor].chunks <= s->max_items; };
         if (s->cfg.policy == SRM3_SERVE_SHORTEST_FIRST) {
             std::vector<size_t> pri(s->order.size());
             for (size_t i = 0; i < pri.size(); ++i) pri[i] = i;
@@ -383,11 +393,11 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
                              [&](size_t a, size_t b) { return s->order[a]->left < s->order[b]->left; });
             for (size_t i : pri) {
                 SReq *q = s->order[i];
-                while (q->cursor < q->items.size() && !full()) {
+                while (q->cursor < q->items.size() && !full() && room(q)) {
                     take[i].push_back(q->items[q->cursor++]);
                     spent += take[i].back().cost;
                     q->left -= take[i].back().cost;
-                    ++n_items;
+                    n_items += take[i].back().chunks;
                 }
                 if (full()) break;
             }
@@ -397,11 +407,11 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
                 more = false;
                 for (size_t i = 0; i < s->order.size() && !full(); ++i) {
                     SReq *q = s->order[i];
-                    if (q->cursor >= q->items.size()) continue;
+                    if (q->cursor >= q->items.size() || !room(q)) continue;
                     take[i].push_back(q->items[q->cursor++]);
                     spent += take[i].back().cost;
                     q->left -= take[i].back().cost;
-                    ++n_items;
+                    n_items += take[i].back().chunks;
                     more = true;
                 }
             }
@@ -421,15 +431,33 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         int k = 0, q_ix = 1;
         double acc = 0.0;
         qb[0] = 0;
-        for (size_t i = 0; i < take.size(); ++i)
+        SplitList split;
+        double plain = 0.0;   // cost of the persistent launch's items
+        for (size_t i = 0; i < take.size(); ++i) {
+            const SReq *q = s->order[i];
+            if (q->split) {
+                std::vector<SplitTile> tiles;
+                for (const Item &it : take[i]) tiles.push_back({q->slot, it.kb, it.cg, it.chunks, it.cost});
+                split.add(split_shape(q->g), tiles);
+            } else {
+                for (const Item &it : take[i]) plain += it.cost;
+            }
+        }
+        for (size_t i = 0; i < take.size(); ++i) {
+            if (s->order[i]->split) continue;
             for (const Item &it : take[i]) {
-                while (q_ix < kXcds && acc >= spent * q_ix / kXcds) qb[q_ix++] = k;
+                while (q_ix < kXcds && acc >= plain * q_ix / kXcds) qb[q_ix++] = k;
                 fill_persistent_item(P + s->off_items + ib * k, s->order[i]->slot, it.kb, it.cg);
                 acc += it.cost;
                 ++k;
             }
+        }
         while (q_ix <= kXcds) qb[q_ix++] = k;
-        const size_t bytes = s->off_items + ib * static_cast<size_t>(std::max(k, 1));
+        SplitItems split_n;
+        const std::vector<unsigned char> sitems = split.items(&split_n);
+        const size_t off_split = s->off_items + ib * static_cast<size_t>(k);
+        if (!sitems.empty()) std::memcpy(P + off_split, sitems.data(), sitems.size());
+        const size_t bytes = off_split + std::max(sitems.size(), ib);
         hipStream_t st = s->lane[c];
         const int o = c ^ 1;
         hipError_t e = hipMemcpyAsync(s->dev_stage[c].p, P, bytes, hipMemcpyHostToDevice, st);
@@ -450,8 +478,9 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
             }
             Workspace wp = ws;
             if (q->mode != 0) wp.zcol = nullptr;   // no a operand planes needed
-            e = launch_phases(q->g, s->cfg.precision, nullptr, &hdr_dev[q->slot].seed, 1, wp,
-                              static_cast<const double *>(q->r.plan->lr.p), st);
+            e = q->split ? launch_phases_split(q->g, nullptr, &hdr_dev[q->slot].seed, 1, wp, st)
+                         : launch_phases(q->g, s->cfg.precision, nullptr, &hdr_dev[q->slot].seed, 1, wp,
+                                         static_cast<const double *>(q->r.plan->lr.p), st);
             if (e != hipSuccess) return dev_err(e, "phase kernel");
             if (q->mode == 1) {
                 // the whole pair sum of this request, here on the lane
@@ -467,6 +496,12 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         if (s->recorded[o] && (e = hipStreamWaitEvent(st, s->ev_phases[o], 0)) != hipSuccess)
             return dev_err(e, "hipStreamWaitEvent");
         // ---- pair sums ----
+        if (split.tiles() > 0) {
+            char *D = static_cast<char *>(s->dev_stage[c].p);
+            e = launch_pairsum_split_items(D + s->off_req, D + off_split, split_n, split.tiles(),
+                                           static_cast<unsigned *>(s->split_ctr[c].p), st);
+            if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
+        }
         if (k > 0) {
             char *D = static_cast<char *>(s->dev_stage[c].p);
             e = launch_pairsum_persistent(s->cfg.precision, s->R, D + s->off_req, D + s->off_items,
