@@ -249,7 +249,11 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
 /* Pair-sum algorithm of a plan (used by every entry point that takes the plan:
  * generation, coefficients, batches, the server).
  *   SRM3_ALGO_DIRECT     enumerates the unordered pairs of every line (the
- *                        coefficient sum of Section 4.1 / 4.3 as written).
+ *                        coefficient sum of Section 4.1 / 4.3 as written), on
+ *                        the vector ALUs, or in FP32 with n_kappa >= 32 and partner
+ *                        factors (line_r, wind, product) of magnitude 0 or
+ *                        1/64 .. 32 in split FP16 on the matrix cores (see
+ *                        SRM3_ALGO_MFMA).
  *   SRM3_ALGO_KAPPA_FFT  the same sum, reorganised: the weights depend on the
  *                        frequency indices only, so the kappa part of the
  *                        ordered pair sum is a linear convolution of phase
@@ -272,8 +276,8 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *                        phase rows with a block of weighted phases, evaluated
  *                        with 16x16x4 MFMAs (FP32: v_mfma_f32_16x16x4_f32 with
  *                        two-sum flushes; FP64: v_mfma_f64_16x16x4_f64).  FP32
- *                        plans with the default tile shape, unit phases (no
- *                        line_r, wind or product factors) and n_kappa >= 32 take
+ *                        plans with the default tile shape, n_kappa >= 32 and
+ *                        partner factors of moderate range (as above) take
  *                        each FP32 product as three FP16 products of split
  *                        phases with FP32 sums, as accurate as the FP32 form
  *                        (v_mfma_f32_16x16x32_f16).  Same
@@ -466,8 +470,8 @@ typedef struct {
     size_t hbm_budget;        /* bytes of the device arena holding request workspaces (allocated once) */
     double step_pair_terms;   /* minimum pair terms per step; <= 0: 2e11 */
     int32_t policy;           /* SRM3_SERVE_SHORTEST_FIRST or SRM3_SERVE_ROUND_ROBIN */
-    int32_t pair_kernel;      /* SRM3_ALGO_DIRECT (0: vector ALUs) or SRM3_ALGO_MFMA (matrix cores): the
-                                 kernel of the per-step persistent pair-sum launch; direct-form requests
+    int32_t pair_kernel;      /* SRM3_ALGO_DIRECT (0) or SRM3_ALGO_MFMA: the algorithm of the per-step
+                                 persistent pair-sum launches; direct-form requests
                                  must have plans with this algorithm (else SRM3_E_UNSUPPORTED) */
     int32_t mfma_shape;       /* matrix-core tile shape of those launches (0..2, see srm3_plan_set_mfma_shape) */
 } srm3_server_config;

@@ -106,12 +106,15 @@ srm3_status refresh_amp_table(srm3_plan_t p, hipStream_t st)
     return SRM3_OK;
 }
 
-// The matrix-core form with the default tile shape (32 x 32 lines per wave on
-// the FP32 path) takes its products in split FP16 where the phases are unit.
+// The direct form in FP32 runs in split FP16 where the phase factors (with
+// their line factors) have magnitudes that two FP16 parts hold: as the
+// default algorithm, and as SRM3_ALGO_MFMA with the default tile shape (another
+// shape asks for the FP32 MFMAs).  200x900 lines, 16 realizations: 44.2 ms on
+// the vector ALUs, 11.0 ms so.
 bool split_plan(srm3_plan_t p, int shape)
 {
-    return p->algo == SRM3_ALGO_MFMA && shape == 0 && !p->gaussian && !p->hashed &&
-           split_supported(p->g, p->precision, p->lr.p != nullptr);
+    const bool direct = p->algo == SRM3_ALGO_DIRECT || (p->algo == SRM3_ALGO_MFMA && shape == 0);
+    return direct && !p->gaussian && !p->hashed && p->split_range && split_supported(p->g, p->precision);
 }
 
 double max_sigma(double max_sig, double cap, double scale)
@@ -255,7 +258,7 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     Workspace wp = ws;
     if (p->gaussian || p->hashed || kfft_family(p->algo)) wp.zcol = nullptr;   // no a operand planes needed
     const bool split = split_form(p);
-    hipError_t e = split ? launch_phases_split(p->g, seeds, nullptr, batch, wp, st)
+    hipError_t e = split ? launch_phases_split(p->g, seeds, nullptr, batch, wp, static_cast<const double *>(p->lr.p), st)
                          : launch_phases(p->g, p->precision, seeds, nullptr, batch, wp,
                                          static_cast<const double *>(p->lr.p), st);
     if (e != hipSuccess) return dev_err(e, "phase kernel");
@@ -584,6 +587,10 @@ srm3_status srm3_plan(const srm3_grid *grid, const srm3_spectrum *spectrum, cons
     if ((s = upload_bytes(p->S, S, nlines * sizeof(double), st))) return s;
     if ((s = upload_bytes(p->sig, sig.data(), nlines * sizeof(double), st))) return s;
     if (!lcx.empty() && (s = upload_bytes(p->lc, lcx.data(), lcx.size() * sizeof(double), st))) return s;
+    for (size_t l = 0; l < lrx.size() / 2; ++l) {
+        const double r = std::hypot(lrx[2 * l], lrx[2 * l + 1]);
+        if (r > kSplitMaxFactor || (r > 0.0 && r < kSplitMinFactor)) p->split_range = false;
+    }
     if (!lrx.empty() && (s = upload_bytes(p->lr, lrx.data(), lrx.size() * sizeof(double), st))) return s;
     if (!hcx.empty() && (s = upload(p->wtab, hcx, precision, st))) return s;   // the prescribed H as the weights
     if ((s = upload(p->tw_t, pass_twiddles(nt), precision, st))) return s;
@@ -1273,7 +1280,8 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
         if (gr.mode != 0) ws.zcol = nullptr;   // no a operand planes needed
         const uint64_t *seeds = static_cast<const uint64_t *>(b->seeds.p) + gr.first;
         const int nb = static_cast<int>(gr.members.size());
-        hipError_t e = gr.split ? launch_phases_split(gr.g, nullptr, seeds, nb, ws, st)
+        hipError_t e = gr.split ? launch_phases_split(gr.g, nullptr, seeds, nb, ws,
+                                                      static_cast<const double *>(gr.plan->lr.p), st)
                                 : launch_phases(gr.g, b->precision, nullptr, seeds, nb, ws,
                                                 static_cast<const double *>(gr.plan->lr.p), st);
         if (e != hipSuccess) return dev_err(e, "phase kernel");

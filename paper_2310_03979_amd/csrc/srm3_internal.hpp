@@ -153,11 +153,14 @@ hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, cons
                                const Workspace &ws, hipStream_t st);
 // The FP32 direct form on the FP16 matrix cores with split phases (see
 // srm3_split.hip): its phase kernel (the a operand region of the workspace
-// then holds the FP16 parts) and pair sum, for unit phases (no line factors).
+// then holds the FP16 parts) and pair sum, for phase factors of magnitude zero
+// or between the bounds (2^10 z must stay below 65504, and the low part above
+// the subnormals for all but the smallest components).
+constexpr double kSplitMaxFactor = 32.0, kSplitMinFactor = 1.0 / 64;
 constexpr int kSplitMinRows = 32;   // (the FP16 parts fit the a operand region from 30 rows on)
-bool split_supported(const Geometry &g, int precision, bool line_factors);
+bool split_supported(const Geometry &g, int precision);
 hipError_t launch_phases_split(const Geometry &g, const uint64_t *seeds, const uint64_t *seeds_dev, int batch,
-                               const Workspace &ws, hipStream_t st);
+                               const Workspace &ws, const double *lr, hipStream_t st);
 hipError_t launch_pairsum_split(const Geometry &g, const void *wtab, int batch, const Workspace &ws, hipStream_t st);
 // The same over a work list: items (request, row tile, column tile, chunk of
 // partner columns) grouped by tile shape (shape i from begin[i] to
@@ -352,6 +355,7 @@ struct srm3_plan_s {
     srm3::DevBuf amp_t;   // per-line (A_pure, A_pair) at unit scale (plans without line factors)
     srm3::DevBuf lc, lr;     // per-line complex bicoherence factors c, rho (interleaved FP64), or empty
     int ws_batch = 0;
+    bool split_range = true;   // the phase factors' magnitudes suit the split-FP16 pair sum
     bool gaussian = false;   // zero bicoherence: no pair sum (2nd-order SRM)
     bool process = false;    // the 1-D process: one kappa line, one-sided spectrum and pairs
     bool hashed = false;     // bispectrum generated per pair in the kernel (SRM3_BISPEC_HASHED)

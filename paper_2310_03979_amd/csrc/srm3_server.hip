@@ -478,7 +478,8 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
             }
             Workspace wp = ws;
             if (q->mode != 0) wp.zcol = nullptr;   // no a operand planes needed
-            e = q->split ? launch_phases_split(q->g, nullptr, &hdr_dev[q->slot].seed, 1, wp, st)
+            e = q->split ? launch_phases_split(q->g, nullptr, &hdr_dev[q->slot].seed, 1, wp,
+                                               static_cast<const double *>(q->r.plan->lr.p), st)
                          : launch_phases(q->g, s->cfg.precision, nullptr, &hdr_dev[q->slot].seed, 1, wp,
                                          static_cast<const double *>(q->r.plan->lr.p), st);
             if (e != hipSuccess) return dev_err(e, "phase kernel");

@@ -7,9 +7,9 @@
 // splits count every pair twice and the self pair once, whose other half the
 // assembly adds).  For one partner column iw the inner sum is a product of the
 // lower-triangular Toeplitz matrix of column iw with the phase columns jw, and
-// its operands are raw phase factors, |z| = 1: they split exactly into two
-// FP16 parts,
-//     2^10 z = hi + lo + e,  |e| <= 2^-24 2^10,
+// its operands are raw phase factors (times line factors of moderate range),
+// so that each splits into two FP16 parts,
+//     2^10 z = hi + lo + e,  |e| <= 2^-24 2^10 for |z| <= 1,
 // so that three FP16 products (hi hi + hi lo + lo hi) with FP32 accumulation
 // replace one FP32 product: 12 FP16 multiply-adds per pair term at 16 times
 // the FP32 matrix rate.  What a product drops (lo lo and e) is below 2^-23 of
@@ -47,7 +47,7 @@ __host__ __device__ inline int split_seg(int nk) { return split_nk8(nk) + 8; }
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const uint64_t *__restrict__ seeds_dev,
                                                           int b0, Geometry g, float2 *__restrict__ zrow,
-                                                          _Float16 *__restrict__ zh)
+                                                          _Float16 *__restrict__ zh, const double *__restrict__ lr)
 {
     constexpr int TR = 64;
     __shared__ _Float16 at[4][64][TR + 2];   // odd dword stride: columns on distinct banks
@@ -84,8 +84,9 @@ __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const
         const int kk = k0 + kt;
         double s = 0.0, co = 0.0;   // rows past n_kappa hold zero
         if (c >= 0 && c < g.nc && kk < g.nk) {
-            phase_cs(wt[kt][ct], ptab, co, s);
-            zrow[static_cast<long>(b) * g.nk * g.nc + static_cast<long>(kk) * g.nc + c] =
+            const long l = static_cast<long>(kk) * g.nc + c;
+            phase_line(wt[kt][ct], ptab, lr, l, co, s);
+            zrow[static_cast<long>(b) * g.nk * g.nc + l] =
                 make_float2(static_cast<float>(co), static_cast<float>(s));
         }
         if (planes) {
@@ -612,16 +613,12 @@ hipError_t prepare_split_t()
 
 }  // namespace
 
-// Line factors ride on the phases and may span any range, which two FP16
-// parts do not hold; below 32 rows half of every 64-row tile would be idle and
-// the operand region too small.
-bool split_supported(const Geometry &g, int precision, bool line_factors)
-{
-    return precision == SRM3_FP32 && !line_factors && g.nk >= kSplitMinRows;
-}
+// Below 32 rows half of every 64-row tile would be idle and the operand region
+// too small.
+bool split_supported(const Geometry &g, int precision) { return precision == SRM3_FP32 && g.nk >= kSplitMinRows; }
 
 hipError_t launch_phases_split(const Geometry &g, const uint64_t *seeds, const uint64_t *seeds_dev, int batch,
-                               const Workspace &ws, hipStream_t st)
+                               const Workspace &ws, const double *lr, hipStream_t st)
 {
     const int chunk = seeds_dev ? 65535 : kMaxSeedsPerLaunch;
     for (int b0 = 0; b0 < batch; b0 += chunk) {
@@ -633,7 +630,7 @@ hipError_t launch_phases_split(const Geometry &g, const uint64_t *seeds, const u
         const unsigned gx = static_cast<unsigned>((g.nw - kwb + 63) / 64);
         const unsigned gy = static_cast<unsigned>((split_nk8(g.nk) + 63) / 64);
         phase_split_kernel<<<dim3(gx, gy, nb), 256, 0, st>>>(sc, seeds_dev, b0, g, static_cast<float2 *>(ws.zrow),
-                                                             static_cast<_Float16 *>(ws.zcol));
+                                                             static_cast<_Float16 *>(ws.zcol), lr);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

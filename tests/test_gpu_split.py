@@ -86,3 +86,24 @@ def test_alone_equals_in_a_batch_and_poisoned(lib, nk):
     for r in (0, 6):
         lib.srm3_workspace_fill(plan, 1, 0x7FC00000)
         assert torch.equal(_coeffs(lib, plan, [int(seeds[r])])[0], many[r])
+
+
+@pytest.mark.parametrize("algorithm", ["direct", "mfma"])
+@pytest.mark.parametrize("factor", [1.0, 2.0 ** -6, 32.0, 2.0 ** -7])
+def test_line_factors_at_the_bounds(lib, oracle_mod, algorithm, factor):
+    """Partner factors spread over two octaves at both ends of the range the
+    split form takes (and past its lower end, where the FP32 forms run):
+    coefficients against the oracle."""
+    nk, nw, W = 34, 30, 30
+    wl = inp.small_grid(nk, nw, support_w=W, batch=1, seed_base=77)
+    rng = np.random.default_rng(3)
+    r = factor * 2.0 ** (rng.uniform(0.0, 2.0, size=(nk, 2 * nw - 1)) * (-1 if factor > 1 else 1))
+    b2 = inp.random_b2_dense(W, 4, scale=0.2)
+    print(f"[gpu] split factors {algorithm} {factor}", flush=True)
+    bis = dict(kind="dense", b2=b2, beta_mode="seeded", beta_seed=11, support_w=W, cap=0.9, line_r=r)
+    plan = lib.srm3_plan(wl.grid_dict(), wl.spectrum(), bis, "fp32")
+    lib.srm3_plan_set_algorithm(plan, algorithm)
+    C = _coeffs(lib, plan, [5]).cpu().numpy().astype(np.complex128)[0]
+    P = oracle_mod.Problem(nk, nw, W, wl.d_kappa, wl.d_omega, wl.spectrum(), b2, oracle_mod.biphase(W, 11), 0.9, line_r=r)
+    ref = P.coefficients(seed=5)
+    assert np.linalg.norm(C - ref) <= TOL * np.linalg.norm(ref)
