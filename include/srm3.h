@@ -250,7 +250,8 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  * generation, coefficients, batches, the server).
  *   SRM3_ALGO_DIRECT     enumerates the unordered pairs of every line (the
  *                        coefficient sum of Section 4.1 / 4.3 as written), on
- *                        the vector ALUs, or in FP32 with n_kappa >= 32 and partner
+ *                        the vector ALUs, or in FP64 with n_kappa >= 16 on the
+ *                        matrix cores, or in FP32 with n_kappa >= 32 and partner
  *                        factors (line_r, wind, product) of magnitude 0 or
  *                        1/64 .. 32 in split FP16 on the matrix cores (see
  *                        SRM3_ALGO_MFMA).

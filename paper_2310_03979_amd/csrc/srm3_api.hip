@@ -106,15 +106,19 @@ srm3_status refresh_amp_table(srm3_plan_t p, hipStream_t st)
     return SRM3_OK;
 }
 
-// The direct form in FP32 runs in split FP16 where the phase factors (with
-// their line factors) have magnitudes that two FP16 parts hold: as the
-// default algorithm, and as SRM3_ALGO_MFMA with the default tile shape (another
-// shape asks for the FP32 MFMAs).  200x900 lines, 16 realizations: 44.2 ms on
-// the vector ALUs, 11.0 ms so.
-bool split_plan(srm3_plan_t p, int shape)
+// Kernel of a plan's direct-form pair sum (shape: the matrix-core tile shape).
+// FP32 runs in split FP16 where the phase factors (with their line factors)
+// have magnitudes that two FP16 parts hold: as the default algorithm, and as
+// SRM3_ALGO_MFMA with the default tile shape (another shape asks for the FP32
+// MFMAs).  200x900 lines, 16 realizations: 44.2 ms on the vector ALUs, 10.4 so.
+// FP64 takes the FP64 MFMAs from 16 rows on (half a tile): 32x64 lines, one
+// realization, 0.32 ms on the vector ALUs, 0.09 so; 123x777, six: 11.5, 4.2.
+DirectForm direct_form(srm3_plan_t p, int shape)
 {
-    const bool direct = p->algo == SRM3_ALGO_DIRECT || (p->algo == SRM3_ALGO_MFMA && shape == 0);
-    return direct && !p->gaussian && !p->hashed && p->split_range && split_supported(p->g, p->precision);
+    if (p->algo == SRM3_ALGO_MFMA && shape != 0) return DirectForm::mfma;
+    if (p->split_range && split_supported(p->g, p->precision)) return DirectForm::split;
+    if (p->algo == SRM3_ALGO_MFMA || (p->precision == SRM3_FP64 && p->g.nk >= 16)) return DirectForm::mfma;
+    return DirectForm::vector;
 }
 
 double max_sigma(double max_sig, double cap, double scale)
@@ -213,7 +217,6 @@ srm3_status event_pair(srm3_plan_t p, int kernel, hipStream_t st, bool begin)
 // The pair-sum algorithms that go through a DFT along kappa (own workspace and tables).
 bool kfft_family(int algo) { return algo == SRM3_ALGO_KAPPA_FFT || algo == SRM3_ALGO_FFT2D; }
 
-bool split_form(srm3_plan_t p) { return split_plan(p, p->mfma_shape); }
 
 srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
 {
@@ -225,6 +228,10 @@ srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
             return fail(SRM3_E_NOMEM, "workspace hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
         }
         p->ws_batch = batch;
+        // small FP64 grids (without it the sums take a little longer)
+        if (p->precision == SRM3_FP64 && !p->gaussian && !p->hashed && !p->slabs.p &&
+            mfma_slab_bytes(p->g, 1) <= kSlabBytes && p->slabs.alloc(kSlabBytes) != hipSuccess)
+            (void)hipGetLastError();
     }
     if (kfft_family(p->algo) && batch > p->kws_batch) {
         const size_t bytes = kfft_workspace_bytes(p->g, p->kg, p->precision, batch);
@@ -257,7 +264,11 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     if ((s = event_pair(p, 0, st, true))) return s;
     Workspace wp = ws;
     if (p->gaussian || p->hashed || kfft_family(p->algo)) wp.zcol = nullptr;   // no a operand planes needed
-    const bool split = split_form(p);
+    // (the tile shape of SRM3_ALGO_DIRECT is the default one)
+    const int shape = p->algo == SRM3_ALGO_MFMA ? p->mfma_shape : 0;
+    const bool direct = !p->gaussian && !p->hashed && !kfft_family(p->algo);
+    const DirectForm form = direct ? direct_form(p, shape) : DirectForm::vector;
+    const bool split = form == DirectForm::split;
     hipError_t e = split ? launch_phases_split(p->g, seeds, nullptr, batch, wp, static_cast<const double *>(p->lr.p), st)
                          : launch_phases(p->g, p->precision, seeds, nullptr, batch, wp,
                                          static_cast<const double *>(p->lr.p), st);
@@ -274,8 +285,8 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     } else if (split) {
         e = launch_pairsum_split(p->g, p->wtab.p, batch, ws, st);
         if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
-    } else if (p->algo == SRM3_ALGO_MFMA) {
-        e = launch_pairsum_mfma(p->g, p->precision, p->mfma_shape, p->wtab.p, batch, ws, st);
+    } else if (form == DirectForm::mfma) {
+        e = launch_pairsum_mfma(p->g, p->precision, shape, p->wtab.p, batch, ws, Slabs{p->slabs.p, p->slabs.n}, st);
         if (e != hipSuccess) return dev_err(e, "matrix-core pair-sum kernel");
     } else {
         e = launch_pairsum(p->g, p->precision, p->wtab.p, batch, ws, st);
@@ -1087,19 +1098,25 @@ struct srm3_batch_s {
         Geometry g;                    // with the batch's R
         size_t ws_off = 0;
         int first = 0;                 // offset of the group in the device arrays
-        bool split = false;            // mode 0 in split FP16: its items are in the split launch
+        DirectForm form = DirectForm::vector;   // of mode 0: the launch its items are in
         int mode = 0;                  // 0: items of the persistent launch; 1: the plan's kappa-DFT
                                        // pair sum over the group; 2: zero bicoherence, no pair sum
         size_t kws_off = 0;            // kappa-DFT workspace of the group (mode 1)
     };
     std::vector<Group> groups;
     int R = 0;                         // rows per wave of the persistent launch
-    bool mfma = false;                 // its items are those of the matrix-core pair sum
+    bool mfma = false;                 // the plans' algorithm is SRM3_ALGO_MFMA
     int mfma_shape = 0;                // and their tile shape
     int blocks_per_cu = 2;
     int n_cu = 256;
-    DevBuf ws, seeds, scales, sptr, outs, preq, pitem, qbegin, qnext;
-    int n_items = 0, plain_items = 0;  // all work items; those of the persistent launch
+    DevBuf ws, seeds, scales, sptr, outs, preq;
+    // work lists of the persistent launches: vector items, matrix-core items
+    struct Queue {
+        DevBuf items, begin, next;
+        int n = 0;
+    };
+    Queue queue[2];
+    int n_items = 0;                   // all work items
     DevBuf split_items, split_ctr;     // work list of the split-FP16 pair sum and its counters
     SplitItems split_n;
     int split_tiles = 0;
@@ -1164,7 +1181,7 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
     for (auto &gr : b->groups) {
         gr.g = gr.plan->g;
         gr.mode = gr.plan->gaussian ? 2 : (kfft_family(gr.plan->algo) ? 1 : 0);
-        gr.split = gr.mode == 0 && split_plan(gr.plan, b->mfma_shape);
+        if (gr.mode == 0) gr.form = direct_form(gr.plan, b->mfma_shape);
         if (gr.mode == 0) {
             gr.g.R = rows_for(gr.g.nk, b->precision, R);
             gr.g.nkp = ((gr.g.nk + gr.g.R - 1) / gr.g.R) * gr.g.R;
@@ -1193,35 +1210,38 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
         int req, kb, cg;
         double cost;
     };
-    std::vector<std::vector<It>> per_req(b->n);
-    std::vector<double> req_cost(b->n, 0.0);
     const size_t e = b->precision == SRM3_FP64 ? 8 : 4;
     SplitList split;
+    srm3_status s;
+    std::vector<std::vector<It>> per_req[2];   // vector, matrix-core items
+    std::vector<double> req_cost(b->n, 0.0);
+    for (auto &v : per_req) v.resize(b->n);
     for (auto &gr : b->groups) {
+        if (gr.mode != 0) continue;   // no items in the persistent launches
         const Workspace ws = carve_workspace(gr.g, b->precision, static_cast<int>(gr.members.size()),
                                              static_cast<char *>(b->ws.p) + gr.ws_off);
         const size_t lines = static_cast<size_t>(gr.g.nk) * gr.g.nc;
-        const size_t a_bytes = gr.split ? split_operand_bytes(gr.g) : a_slots(b->precision) * gr.g.ncw * gr.g.nkp * e;
+        const size_t a_bytes = gr.form == DirectForm::split ? split_operand_bytes(gr.g)
+                                                            : a_slots(b->precision) * gr.g.ncw * gr.g.nkp * e;
+        const bool mfma = gr.form == DirectForm::mfma;
         const int mr = mfma_rows_per_group(b->precision, b->mfma_shape);
         const int mc = mfma_cols_per_group(b->precision, b->mfma_shape);
-        const int nrb = b->mfma ? (gr.g.nk + mr - 1) / mr : gr.g.nkp / gr.g.R;
-        const int ncg = b->mfma ? (gr.g.nc + mc - 1) / mc
-                                : ((gr.g.nc + 63) / 64 + waves_per_block() - 1) / waves_per_block();
-        if (gr.mode != 0) continue;   // no items in the persistent launch
+        const int nrb = mfma ? (gr.g.nk + mr - 1) / mr : gr.g.nkp / gr.g.R;
+        const int ncg = mfma ? (gr.g.nc + mc - 1) / mc : ((gr.g.nc + 63) / 64 + waves_per_block() - 1) / waves_per_block();
         for (size_t slot = 0; slot < gr.members.size(); ++slot) {
             const int d = gr.first + static_cast<int>(slot);
             fill_persistent_req(reqs.data() + rb * d, gr.g, static_cast<char *>(ws.zrow) + slot * lines * 2 * e,
                                 static_cast<char *>(ws.zcol) + slot * a_bytes,
                                 static_cast<char *>(ws.tsum) + slot * lines * 2 * e, gr.plan->wtab.p);
-            if (gr.split) {
+            if (gr.form == DirectForm::split) {
                 split.add(d, gr.g);
                 continue;
             }
             for (int kb = nrb - 1; kb >= 0; --kb)
                 for (int cg = 0; cg < ncg; ++cg) {
-                    const double c = b->mfma ? mfma_item_cost_impl(gr.g, kb, cg, b->precision, b->mfma_shape)
-                                             : item_cost_impl(gr.g, gr.g.R, kb, cg);
-                    per_req[d].push_back({d, kb, cg, c});
+                    const double c = mfma ? mfma_item_cost_impl(gr.g, kb, cg, b->precision, b->mfma_shape)
+                                          : item_cost_impl(gr.g, gr.g.R, kb, cg);
+                    per_req[mfma][d].push_back({d, kb, cg, c});
                     req_cost[d] += c;
                 }
         }
@@ -1231,44 +1251,48 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
     std::vector<int> order(b->n);
     for (int i = 0; i < b->n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return req_cost[x] > req_cost[y]; });
-    std::vector<It> all;
-    double total = 0.0;
-    for (int d : order) {
-        auto &v = per_req[d];
-        std::stable_sort(v.begin(), v.end(), [](const It &x, const It &y) { return x.cost > y.cost; });
-        for (auto &it : v) {
-            all.push_back(it);
-            total += it.cost;
+    b->n_items = 0;
+    for (int kind = 0; kind < 2; ++kind) {
+        std::vector<It> all;
+        double total = 0.0;
+        for (int d : order) {
+            auto &v = per_req[kind][d];
+            std::stable_sort(v.begin(), v.end(), [](const It &x, const It &y) { return x.cost > y.cost; });
+            for (auto &it : v) {
+                all.push_back(it);
+                total += it.cost;
+            }
+        }
+        auto &qu = b->queue[kind];
+        qu.n = static_cast<int>(all.size());
+        b->n_items += qu.n;
+        if (all.empty()) continue;
+        std::vector<int> qbegin(kXcds + 1, 0);
+        double acc = 0.0;
+        int q = 1;
+        for (size_t i = 0; i < all.size(); ++i) {
+            while (q < kXcds && acc >= total * q / kXcds) qbegin[q++] = static_cast<int>(i);
+            acc += all[i].cost;
+        }
+        while (q <= kXcds) qbegin[q++] = static_cast<int>(all.size());
+        std::vector<unsigned char> items(ib * all.size());
+        for (size_t i = 0; i < all.size(); ++i) fill_persistent_item(items.data() + ib * i, all[i].req, all[i].kb, all[i].cg);
+        if ((s = upload_bytes(qu.items, items.data(), items.size(), st))) return s;
+        if ((s = upload_bytes(qu.begin, qbegin.data(), qbegin.size() * sizeof(int), st))) return s;
+        if (!qu.next.p) {
+            const hipError_t er = qu.next.alloc(kXcds * sizeof(int));
+            if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
         }
     }
-    std::vector<int> qbegin(kXcds + 1, 0);
-    double acc = 0.0;
-    int q = 1;
-    for (size_t i = 0; i < all.size(); ++i) {
-        while (q < kXcds && acc >= total * q / kXcds) qbegin[q++] = static_cast<int>(i);
-        acc += all[i].cost;
-    }
-    while (q <= kXcds) qbegin[q++] = static_cast<int>(all.size());
-    std::vector<unsigned char> items(ib * std::max<size_t>(1, all.size()));
-    for (size_t i = 0; i < all.size(); ++i) fill_persistent_item(items.data() + ib * i, all[i].req, all[i].kb, all[i].cg);
     const std::vector<unsigned char> sitems = split.items(&b->split_n);
     b->split_tiles = split.tiles();
-    b->n_items = static_cast<int>(all.size()) + b->split_n.begin[kSplitShapes];
-    b->plain_items = static_cast<int>(all.size());
-    srm3_status s;
+    b->n_items += b->split_n.begin[kSplitShapes];
     if (b->split_tiles > 0) {
         if ((s = upload_bytes(b->split_items, sitems.data(), sitems.size(), st))) return s;
         const hipError_t er = b->split_ctr.alloc(split_counter_words(b->split_tiles) * sizeof(unsigned));
         if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
     }
-    if ((s = upload_bytes(b->preq, reqs.data(), reqs.size(), st))) return s;
-    if ((s = upload_bytes(b->pitem, items.data(), items.size(), st))) return s;
-    if ((s = upload_bytes(b->qbegin, qbegin.data(), qbegin.size() * sizeof(int), st))) return s;
-    if (!b->qnext.p) {
-        hipError_t er = b->qnext.alloc(kXcds * sizeof(int));
-        if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
-    }
-    return SRM3_OK;
+    return upload_bytes(b->preq, reqs.data(), reqs.size(), st);
 }
 
 // The launch sequence of one run (stream-ordered; capturable).
@@ -1280,7 +1304,7 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
         if (gr.mode != 0) ws.zcol = nullptr;   // no a operand planes needed
         const uint64_t *seeds = static_cast<const uint64_t *>(b->seeds.p) + gr.first;
         const int nb = static_cast<int>(gr.members.size());
-        hipError_t e = gr.split ? launch_phases_split(gr.g, nullptr, seeds, nb, ws,
+        hipError_t e = gr.mode == 0 && gr.form == DirectForm::split ? launch_phases_split(gr.g, nullptr, seeds, nb, ws,
                                                       static_cast<const double *>(gr.plan->lr.p), st)
                                 : launch_phases(gr.g, b->precision, nullptr, seeds, nb, ws,
                                                 static_cast<const double *>(gr.plan->lr.p), st);
@@ -1302,10 +1326,13 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
                                        static_cast<unsigned *>(b->split_ctr.p), st);
         if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
     }
-    if (b->plain_items > 0) {
-        e = launch_pairsum_persistent(b->precision, b->R, b->preq.p, b->pitem.p,
-                                      static_cast<const int *>(b->qbegin.p), static_cast<int *>(b->qnext.p),
-                                      b->n_cu * b->blocks_per_cu, st, b->mfma, b->mfma_shape);
+    for (int kind = 0; kind < 2; ++kind) {
+        const auto &qu = b->queue[kind];
+        if (qu.n == 0) continue;
+        e = launch_pairsum_persistent(b->precision, b->R, b->preq.p, qu.items.p, static_cast<const int *>(qu.begin.p),
+                                      static_cast<int *>(qu.next.p),
+                                      b->n_cu * (kind == 1 && !b->mfma ? kMfmaBlocksPerCu : b->blocks_per_cu), st,
+                                      kind == 1, b->mfma_shape);
         if (e != hipSuccess) return dev_err(e, "persistent pair-sum kernel");
     }
     if (time_pairsum) (void)hipEventRecord(b->ev_b, st);
@@ -1441,7 +1468,7 @@ srm3_status srm3_batch_create(const srm3_request *reqs, int32_t n, int32_t flags
     b->n = n;
     b->flags = flags;
     b->mfma = has_mfma;
-    if (has_mfma) b->blocks_per_cu = 3;   // the matrix-core kernel runs 3 waves per SIMD
+    if (has_mfma) b->blocks_per_cu = kMfmaBlocksPerCu;
     b->req.assign(reqs, reqs + n);
     std::map<srm3_plan_t, int> gi;
     for (int i = 0; i < n; ++i) {

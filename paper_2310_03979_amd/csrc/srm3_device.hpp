@@ -107,6 +107,49 @@ __device__ __forceinline__ void phase_line(uint32_t u, const double2 *ptab, cons
     }
 }
 
+// Ordered additions to a sum by several waves or blocks, counted: one waits
+// until n are counted, adds, and counts itself once its stores are done.  The
+// sums are read and written with agent-scope (coherent) accesses, so no cache
+// has to be written back or invalidated around them: with fences instead, one
+// addition in a launch of 3072 waves cost over 200 us.
+__device__ __forceinline__ unsigned load_count(const unsigned *count)
+{
+    return __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void wait_count(const unsigned *count, unsigned n)
+{
+    while (load_count(count) < n) __builtin_amdgcn_s_sleep(8);
+    asm volatile("" ::: "memory");
+}
+
+// Wait for the wave's own stores.
+__device__ __forceinline__ void wait_stores()
+{
+    asm volatile("" ::: "memory");
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0);
+#endif
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ void set_count(unsigned *count, unsigned n)
+{
+    __hip_atomic_store(count, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+__device__ __forceinline__ T coherent_load(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+__device__ __forceinline__ void coherent_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Descriptor of one request of a persistent launch, and one of its work items.
 struct PReq {
     Geometry g;

@@ -149,8 +149,19 @@ struct MfmaShape {
 };
 constexpr int kMfmaShapes = 3;
 MfmaShape mfma_shape(int precision, int shape);
+// `slabs`: device memory for the FP64 form's partial sums of small calls (may be
+// empty; the sums are the same).
+struct Slabs {
+    void *p = nullptr;
+    size_t n = 0;
+};
+constexpr size_t kSlabBytes = size_t(16) << 20;
+size_t mfma_slab_bytes(const Geometry &g, int batch);   // of the default tile shape
+constexpr int kMfmaBlocksPerCu = 3;   // the matrix-core kernels run 3 waves per SIMD
+// Kernels of the direct form: vector ALUs, matrix cores, split FP16.
+enum class DirectForm { vector, mfma, split };
 hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, const void *wtab, int batch,
-                               const Workspace &ws, hipStream_t st);
+                               const Workspace &ws, const Slabs &slabs, hipStream_t st);
 // The FP32 direct form on the FP16 matrix cores with split phases (see
 // srm3_split.hip): its phase kernel (the a operand region of the workspace
 // then holds the FP16 parts) and pair sum, for phase factors of magnitude zero
@@ -355,6 +366,7 @@ struct srm3_plan_s {
     srm3::DevBuf amp_t;   // per-line (A_pure, A_pair) at unit scale (plans without line factors)
     srm3::DevBuf lc, lr;     // per-line complex bicoherence factors c, rho (interleaved FP64), or empty
     int ws_batch = 0;
+    srm3::DevBuf slabs;   // partial sums of small FP64 calls (see Slabs), with the workspace
     bool split_range = true;   // the phase factors' magnitudes suit the split-FP16 pair sum
     bool gaussian = false;   // zero bicoherence: no pair sum (2nd-order SRM)
     bool process = false;    // the 1-D process: one kappa line, one-sided spectrum and pairs
@@ -382,8 +394,6 @@ struct srm3_plan_s {
 
 namespace srm3 {
 AmpRef plan_amp(srm3_plan_t p);
-// Whether the plan's direct-form pair sum runs in split FP16 (shape: the
-// matrix-core tile shape in use).
-bool split_plan(srm3_plan_t p, int shape);
+DirectForm direct_form(srm3_plan_t p, int shape);
 KfftTables plan_ktab(srm3_plan_t p);
 }  // namespace srm3

@@ -6,6 +6,7 @@
 //                (k_kappa, k_omega mod n_t), inverse DFT along t (Stockham, LDS)
 //  xfft        : inverse DFT along x over the n_kappa live rows, real part out
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <string>
 
@@ -616,6 +617,12 @@ struct MfmaArgs {
     int flush_steps;    // kappa steps between two-sum flushes
 };
 
+// Partner columns of a chunk of the FP64 form, by the grid alone (the sums do
+// not depend on the batch).  A wave's item of 32 columns takes 80-160 us at 128
+// rows, long beside the 10 us of an ordered addition; the smallest grids take
+// 8 (11 us at 32x64, 64 waves for one realization), their chunks summed apart.
+__host__ __device__ inline int mfma_chunk(const Geometry &g) { return g.nk * g.nc <= 16384 ? 8 : 32; }
+
 constexpr int kMfmaFlushSteps = 256;   // 1024 products per accumulator element
 constexpr long kMfmaPrioBlocks = 16 * 256;   // launches of at least 16 blocks per CU raise the MFMA priority
 
@@ -647,10 +654,17 @@ template <> struct MfmaT<double> {
 // One wave's RT x CT tiles of one realization: output rows from K0 = 16 RT rg,
 // columns c0 .. c0 + 16 CT - 1.  PRIO: issue each split's MFMAs at raised
 // wave priority.
+//
+// FP64 sums the partner columns in chunks of mfma_chunk(nk) and adds the
+// chunks in order, chunks chunk0 .. chunk1 - 1 here (the tile's last one at
+// most).  Chunk first_chunk starts the sum in tout_b.  With `done` the chunks
+// of a tile may be run by several waves: each waits until those before it are
+// added.
 template <typename T, int RT, int CT, bool PRIO>
 __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<T>::v2 *__restrict__ zrow_b,
                                           const T *__restrict__ zcol_b, const typename vec<T>::v2 *__restrict__ wtab,
-                                          typename vec<T>::v2 *__restrict__ tout_b, int rg, int c0, int flush_steps)
+                                          typename vec<T>::v2 *__restrict__ tout_b, int rg, int c0, int flush_steps,
+                                          int chunk0, int chunk1, int first_chunk, unsigned *done)
 {
     using T2 = typename vec<T>::v2;
     using M = MfmaT<T>;
@@ -663,6 +677,11 @@ __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<
     const int kw_hi = min(c0 + 16 * CT - 1, g.nc - 1) - (g.nw - 1);
     const int iw_lo = max(-Wm1, kw_lo - Wm1);
     const int iw_hi = min(Wm1, kw_hi + Wm1);
+    const int ch = M::COMP ? INT_MAX / 2 : mfma_chunk(g);
+    if (!M::COMP) {
+        chunk1 = min(chunk1, iw_hi < iw_lo ? 1 : (iw_hi - iw_lo) / ch + 1);
+        if (chunk0 >= chunk1) return;
+    }
     const int kk_max = min(K0 + 16 * RT - 1, g.nk - 1);
     const int jk_end = kk_max / 2;   // last kappa split any row of the wave uses
     const int jb = K0 / 2;           // splits below jb are at full weight for every row
@@ -784,8 +803,12 @@ __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<
         if (PRIO) __builtin_amdgcn_s_setprio(0);
     };
 
+    // FP64 sums chunk by chunk, each added to the tile's in order
+    for (int chunk = M::COMP ? 0 : chunk0;;) {
+    const int i0 = M::COMP ? iw_lo : iw_lo + chunk * ch;
+    const int i1 = M::COMP ? iw_hi : min(iw_hi, i0 + ch - 1);
     int since = 0;
-    for (int iw0 = iw_lo; iw0 <= iw_hi; iw0 += 4) {
+    for (int iw0 = i0; iw0 <= i1; iw0 += 4) {
         unsigned ao;
         unsigned boff[CT];
         T2 wc[CT];
@@ -818,6 +841,46 @@ __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<
         }
     }
     flush();
+    // FP64: onto the sums of the chunks before
+    const bool add = !M::COMP && chunk > first_chunk;
+    if (add && done) wait_count(done, static_cast<unsigned>(chunk));
+    T2 v[RT][CT][4];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (M::COMP) {
+                    v[r][c][e].x = sre[r][c][e] + cre[r][c][e];
+                    v[r][c][e].y = sim[r][c][e] + cim[r][c][e];
+                } else {
+                    v[r][c][e].x = P1[r][c][e] - P2[r][c][e];
+                    v[r][c][e].y = P1[r][c][e] + P3[r][c][e];
+                }
+            }
+    if (add) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            T2 old[CT][4];
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const T2 *p = tout_b + static_cast<long>(min(K0 + 16 * r + M::drow(lq, e), g.nk - 1)) * g.nc +
+                                  min(c0 + 16 * c + li, g.nc - 1);
+                    old[c][e].x = coherent_load(&p->x);
+                    old[c][e].y = coherent_load(&p->y);
+                }
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[r][c][e].x += old[c][e].x;
+                    v[r][c][e].y += old[c][e].y;
+                }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -826,17 +889,99 @@ __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int kk = K0 + 16 * r + M::drow(lq, e);
-                T2 v;
-                if constexpr (M::COMP) {
-                    v.x = sre[r][c][e] + cre[r][c][e];
-                    v.y = sim[r][c][e] + cim[r][c][e];
-                } else {
-                    v.x = P1[r][c][e] - P2[r][c][e];
-                    v.y = P1[r][c][e] + P3[r][c][e];
+                if (kk < g.nk && col < g.nc) {
+                    T2 *p = tout_b + static_cast<long>(kk) * g.nc + col;
+                    if (M::COMP) {
+                        *p = v[r][c][e];
+                    } else {
+                        coherent_store(&p->x, v[r][c][e].x);
+                        coherent_store(&p->y, v[r][c][e].y);
+                    }
                 }
-                if (kk < g.nk && col < g.nc) tout_b[static_cast<long>(kk) * g.nc + col] = v;
             }
         }
+    if constexpr (M::COMP) break;
+    ++chunk;
+    if (done) {
+        wait_stores();
+        if (lane == 0) set_count(done, static_cast<unsigned>(chunk));
+    }
+    if (chunk >= chunk1) break;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) P1[r][c] = P2[r][c] = P3[r][c] = V4{T(0), T(0), T(0), T(0)};
+    }
+}
+
+// The FP64 form over a queue of (tile, chunk) items, one wave each, taken in
+// order (chunk by chunk over all tiles) by four waves at a time: a wave waits
+// only for items taken before its own by running waves, or beside it.
+struct MfmaQueue {
+    unsigned *next;   // zero at launch
+    unsigned *done;   // chunks added per wave tile, zero at launch
+    int n_ct;         // column tiles
+    int tiles;        // batch * n_rg * n_ct
+    int n_items;      // tiles * chunks of the widest tile
+    double2 *slabs;   // or null: [chunks][batch][nk][nc], each chunk's sums apart (added by sum_slabs_kernel)
+};
+
+// Chunks of the column tile that starts at column c0.
+__host__ __device__ inline int mfma_tile_chunks(const Geometry &g, int c0, int cols)
+{
+    const int lo = c0 - (g.nw - 1), hi = (c0 + cols - 1 < g.nc - 1 ? c0 + cols - 1 : g.nc - 1) - (g.nw - 1);
+    const int i0 = lo - (g.W - 1) > -(g.W - 1) ? lo - (g.W - 1) : -(g.W - 1);
+    const int i1 = hi + g.W - 1 < g.W - 1 ? hi + g.W - 1 : g.W - 1;
+    return i1 < i0 ? 1 : (i1 - i0) / mfma_chunk(g) + 1;
+}
+
+// The chunks' sums, added in the order of the queue form.
+__global__ __launch_bounds__(256) void sum_slabs_kernel(const double2 *__restrict__ slabs, Geometry g, int batch,
+                                                        int cols, double2 *__restrict__ tout)
+{
+    const long n = static_cast<long>(batch) * g.nk * g.nc;
+    const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int col = static_cast<int>(i % g.nc);
+    const int chunks = mfma_tile_chunks(g, col / cols * cols, cols);
+    double2 t = slabs[i];
+    for (int c = 1; c < chunks; ++c) {
+        const double2 x = slabs[c * n + i];
+        t.x += x.x;
+        t.y += x.y;
+    }
+    tout[i] = t;
+}
+
+template <int RT, int CT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void pairsum_mfma_queue_kernel(MfmaArgs a,
+                                                                                                        MfmaQueue q)
+{
+    const Geometry &g = a.g;
+    const long lines = static_cast<long>(g.nk) * g.nc;
+    const long plane = static_cast<long>(g.ncw) * g.nkp;
+    __shared__ int s_base[2];
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    for (int turn = 0;; turn ^= 1) {
+        // (one atomic per block: 3072 waves on one counter would wait 0.1 ms for their turns)
+        if (threadIdx.x == 0) s_base[turn] = static_cast<int>(atomicAdd(q.next, static_cast<unsigned>(kWavesPerBlock)));
+        __syncthreads();
+        const int base = __builtin_amdgcn_readfirstlane(s_base[turn]);
+        if (base >= q.n_items) return;
+        const int item = base + wave;
+        if (item >= q.n_items) continue;
+        const int chunk = item / q.tiles, tile = item - chunk * q.tiles;
+        // heaviest row groups first, realizations innermost
+        const int k = tile / a.batch, b = tile - k * a.batch;
+        const int rg = a.n_rg - 1 - k / q.n_ct, ct = k - (k / q.n_ct) * q.n_ct;
+        mfma_tile<double, RT, CT, true>(g, static_cast<const double2 *>(a.zrow) + b * lines,
+                                         static_cast<const double *>(a.zcol) + b * ALayout<double>::NS * plane,
+                                         static_cast<const double2 *>(a.wtab),
+                                         q.slabs ? q.slabs + (static_cast<long>(chunk) * a.batch + b) * lines
+                                                 : static_cast<double2 *>(a.tout) + b * lines,
+                                         rg, 16 * CT * ct, a.flush_steps, chunk, chunk + 1, q.slabs ? chunk : 0,
+                                         q.slabs ? nullptr : q.done + tile);
+    }
 }
 
 template <typename T, int RT, int CT, bool PRIO>
@@ -868,7 +1013,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
     const long plane = static_cast<long>(g.ncw) * g.nkp;
     mfma_tile<T, RT, CT, PRIO>(g, static_cast<const T2 *>(a.zrow) + b * lines,
                          static_cast<const T *>(a.zcol) + b * ALayout<T>::NS * plane, static_cast<const T2 *>(a.wtab),
-                         static_cast<T2 *>(a.tout) + b * lines, rg, c0, a.flush_steps);
+                         static_cast<T2 *>(a.tout) + b * lines, rg, c0, a.flush_steps, 0, 1, 0, nullptr);
 }
 
 // Persistent pair sum over an uneven work list.  Work items (request, row
@@ -956,7 +1101,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
         if (c0 < rq.g.nc)
             mfma_tile<T, RT, CT, false>(rq.g, static_cast<const T2 *>(rq.zrow), static_cast<const T *>(rq.zcol),
                                  static_cast<const T2 *>(rq.wtab), static_cast<T2 *>(rq.tsum), w.kb, c0,
-                                 kMfmaFlushSteps);
+                                 kMfmaFlushSteps, 0, INT_MAX, 0, nullptr);
     }
 }
 
@@ -2391,7 +2536,8 @@ hipError_t launch_pairsum(const Geometry &g, int precision, const void *wtab, in
 }
 
 template <typename T, int RT, int CT>
-static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch, const Workspace &ws, hipStream_t st)
+static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch, const Workspace &ws,
+                                 const Slabs &slabs, hipStream_t st)
 {
     MfmaArgs a;
     a.zrow = ws.zrow;
@@ -2404,6 +2550,30 @@ static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch,
     const int n_ct = (g.nc + 16 * CT - 1) / (16 * CT);
     a.n_cg = (n_ct + kWavesPerBlock - 1) / kWavesPerBlock;
     a.flush_steps = kMfmaFlushSteps;
+    if constexpr (sizeof(T) == 8) {
+        // the counters live in the transform workspace, which nothing uses before the t-transform
+        MfmaQueue q;
+        q.next = static_cast<unsigned *>(ws.g);
+        q.done = q.next + 1;
+        q.n_ct = n_ct;
+        q.tiles = batch * a.n_rg * n_ct;
+        int chunks = 1;
+        for (int c0 = 0; c0 < g.nc; c0 += 16 * CT) chunks = std::max(chunks, mfma_tile_chunks(g, c0, 16 * CT));
+        q.n_items = q.tiles * chunks;
+        const long n = static_cast<long>(batch) * g.nk * g.nc;
+        // one call's chunks apart where they fit beside the workspace: no chain
+        // of ordered additions (32x64 lines: 0.17 -> 0.09 ms)
+        q.slabs = chunks > 1 && slabs.p && static_cast<size_t>(chunks) * n * sizeof(double2) <= slabs.n
+                      ? static_cast<double2 *>(slabs.p) : nullptr;
+        const hipError_t e = launch_fill_u32(q.next, 1 + static_cast<size_t>(q.tiles), 0u, st);
+        if (e != hipSuccess) return e;
+        const int blocks = std::min((q.n_items + kWavesPerBlock - 1) / kWavesPerBlock, 3 * 256);
+        pairsum_mfma_queue_kernel<RT, CT><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a, q);
+        if (q.slabs)
+            sum_slabs_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), 256, 0, st>>>(
+                q.slabs, g, batch, 16 * CT, static_cast<double2 *>(ws.tsum));
+        return hipGetLastError();
+    } else {
     const long work = static_cast<long>(a.n_rg) * batch * a.n_cg;
     a.per_xcd = batch >= kNumXcd ? static_cast<int>((work + kNumXcd - 1) / kNumXcd) : 0;
     const long blocks = a.per_xcd > 0 ? static_cast<long>(a.per_xcd) * kNumXcd : work;
@@ -2415,6 +2585,7 @@ static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch,
     else
         pairsum_mfma_kernel<T, RT, CT, false><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a);
     return hipGetLastError();
+    }
 }
 
 // Tile shapes of the matrix-core pair sum: 16 x 16 MFMA tiles per wave,
@@ -2427,20 +2598,28 @@ MfmaShape mfma_shape(int precision, int id)
     return precision == SRM3_FP64 ? f64[id] : f32[id];
 }
 
+size_t mfma_slab_bytes(const Geometry &g, int batch)
+{
+    const int cols = 16 * mfma_shape(SRM3_FP64, 0).ct;
+    int chunks = 1;
+    for (int c0 = 0; c0 < g.nc; c0 += cols) chunks = std::max(chunks, mfma_tile_chunks(g, c0, cols));
+    return static_cast<size_t>(chunks) * batch * g.nk * g.nc * sizeof(double2);
+}
+
 hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, const void *wtab, int batch,
-                               const Workspace &ws, hipStream_t st)
+                               const Workspace &ws, const Slabs &slabs, hipStream_t st)
 {
     if (precision == SRM3_FP64) {
         switch (shape) {
-        case 1: return pairsum_mfma_t<double, 2, 1>(g, wtab, batch, ws, st);
-        case 2: return pairsum_mfma_t<double, 1, 2>(g, wtab, batch, ws, st);
-        default: return pairsum_mfma_t<double, 2, 2>(g, wtab, batch, ws, st);
+        case 1: return pairsum_mfma_t<double, 2, 1>(g, wtab, batch, ws, slabs, st);
+        case 2: return pairsum_mfma_t<double, 1, 2>(g, wtab, batch, ws, slabs, st);
+        default: return pairsum_mfma_t<double, 2, 2>(g, wtab, batch, ws, slabs, st);
         }
     }
     switch (shape) {
-    case 1: return pairsum_mfma_t<float, 2, 1>(g, wtab, batch, ws, st);
-    case 2: return pairsum_mfma_t<float, 1, 2>(g, wtab, batch, ws, st);
-    default: return pairsum_mfma_t<float, 2, 2>(g, wtab, batch, ws, st);
+    case 1: return pairsum_mfma_t<float, 2, 1>(g, wtab, batch, ws, slabs, st);
+    case 2: return pairsum_mfma_t<float, 1, 2>(g, wtab, batch, ws, slabs, st);
+    default: return pairsum_mfma_t<float, 2, 2>(g, wtab, batch, ws, slabs, st);
     }
 }
 

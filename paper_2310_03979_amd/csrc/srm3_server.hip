@@ -59,7 +59,7 @@ struct SReq {
                                     // pair sum, run at admission; 2: zero bicoherence, no pair sum
     size_t kfft_off = 0;            // arena offset of the kappa-DFT workspace (mode 1)
     std::vector<Item> items;        // heaviest first
-    bool split = false;             // pair sum in split FP16: items are tiles of the split launch
+    DirectForm form = DirectForm::vector;   // of mode 0: the launch its items are in (split: tiles)
     size_t cursor = 0;
     double left = 0.0;              // cost of the items not yet issued
     hipEvent_t done = nullptr;
@@ -124,10 +124,10 @@ struct srm3_server_s {
     int mfma_shape = 0;                // their tile shape
     DevBuf arena_mem;
     Arena arena;
-    // staging: headers | qbegin | preq | items
+    // staging: headers | qbegin of the two persistent lists | preq | items
     size_t off_hdr = 0, off_q = 0, off_req = 0, off_items = 0, stage_bytes = 0;
     int max_items = 0;
-    DevBuf dev_stage[2], qnext[2], split_ctr[2];
+    DevBuf dev_stage[2], qnext[2], split_ctr[2];   // qnext: of the vector and the matrix-core list
     unsigned char *pinned[2] = {nullptr, nullptr};
     hipEvent_t copied[2] = {nullptr, nullptr};
     bool copy_pending[2] = {false, false};
@@ -222,7 +222,7 @@ srm3_status srm3_server_create(const srm3_server_config *cfg, void *hip_stream, 
     s->R = cfg->precision == SRM3_FP64 ? 8 : 16;
     s->mfma = cfg->pair_kernel == SRM3_ALGO_MFMA;
     s->mfma_shape = cfg->mfma_shape;
-    if (s->mfma) s->blocks_per_cu = 3;   // the matrix-core kernel runs 3 waves per SIMD
+    if (s->mfma) s->blocks_per_cu = kMfmaBlocksPerCu;
     int dev = 0;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
@@ -234,12 +234,12 @@ srm3_status srm3_server_create(const srm3_server_config *cfg, void *hip_stream, 
     s->max_items = 1 << 17;
     s->off_hdr = 0;
     s->off_q = align256(sizeof(SlotHeader) * na);
-    s->off_req = s->off_q + align256(sizeof(int) * (kXcds + 1));
+    s->off_req = s->off_q + align256(2 * sizeof(int) * (kXcds + 1));
     s->off_items = s->off_req + align256(persistent_req_bytes() * na);
     s->stage_bytes = s->off_items + align256(persistent_item_bytes() * (s->max_items + 1));
     for (int i = 0; i < 2; ++i) {
         if ((e = s->dev_stage[i].alloc(s->stage_bytes)) != hipSuccess ||
-            (e = s->qnext[i].alloc(kXcds * sizeof(int))) != hipSuccess ||
+            (e = s->qnext[i].alloc(2 * kXcds * sizeof(int))) != hipSuccess ||
             (e = s->split_ctr[i].alloc(split_counter_words(s->max_items) * sizeof(unsigned))) != hipSuccess)
             return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
         if ((e = hipStreamCreateWithFlags(&s->lane[i], hipStreamNonBlocking)) != hipSuccess)
@@ -309,20 +309,22 @@ srm3_status srm3_server_submit(srm3_server_t s, const srm3_request *req, const s
     }
     if (q->bytes > s->arena.size)
         return fail(SRM3_E_NOMEM, "request needs %zu bytes, more than the server's budget %zu", q->bytes, s->arena.size);
-    q->split = q->mode == 0 && split_plan(r.plan, s->mfma_shape);
-    if (q->split) {
+    if (q->mode == 0) q->form = direct_form(r.plan, s->mfma ? s->mfma_shape : 0);
+    if (q->mode == 0 && q->form == DirectForm::split) {
         for (const SplitTile &t : split_tiles(q->g, 0))
             q->items.push_back({t.rs, t.cg, t.cost / (64.0 * waves_per_block() * s->R), t.chunks});
         for (const Item &it : q->items) q->left += it.cost;
     } else if (q->mode == 0) {
-        const int mr = mfma_rows_per_group(s->cfg.precision, s->mfma_shape);
-        const int mc = mfma_cols_per_group(s->cfg.precision, s->mfma_shape);
-        const int nrb = s->mfma ? (q->g.nk + mr - 1) / mr : q->g.nkp / q->g.R;
-        const int ncg = s->mfma ? (q->g.nc + mc - 1) / mc
-                                : ((q->g.nc + 63) / 64 + waves_per_block() - 1) / waves_per_block();
+        const bool mfma = q->form == DirectForm::mfma;
+        const int shape = s->mfma ? s->mfma_shape : 0;
+        const int mr = mfma_rows_per_group(s->cfg.precision, shape);
+        const int mc = mfma_cols_per_group(s->cfg.precision, shape);
+        const int nrb = mfma ? (q->g.nk + mr - 1) / mr : q->g.nkp / q->g.R;
+        const int ncg = mfma ? (q->g.nc + mc - 1) / mc : ((q->g.nc + 63) / 64 + waves_per_block() - 1) / waves_per_block();
         for (int kb = nrb - 1; kb >= 0; --kb)
             for (int cg = 0; cg < ncg; ++cg)
-                q->items.push_back({kb, cg, s->mfma ? mfma_item_cost(q->g, kb, cg, s->cfg.precision, s->mfma_shape) : item_cost(q->g, q->g.R, kb, cg)});
+                q->items.push_back({kb, cg, mfma ? mfma_item_cost(q->g, kb, cg, s->cfg.precision, shape)
+                                                 : item_cost(q->g, q->g.R, kb, cg)});
         std::stable_sort(q->items.begin(), q->items.end(),
                          [](const Item &a, const Item &b) { return a.cost > b.cost; });
         for (const Item &it : q->items) q->left += it.cost;
@@ -428,31 +430,35 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         std::memcpy(P + s->off_req, s->preq.data(), s->preq.size());
         int *qb = reinterpret_cast<int *>(P + s->off_q);
         const size_t ib = persistent_item_bytes();
-        int k = 0, q_ix = 1;
-        double acc = 0.0;
-        qb[0] = 0;
         SplitList split;
-        double plain = 0.0;   // cost of the persistent launch's items
+        int k = 0, k0[3] = {0, 0, 0};   // items of the vector list, then of the matrix-core list
+        for (int kind = 0; kind < 2; ++kind) {
+            const DirectForm form = kind == 0 ? DirectForm::vector : DirectForm::mfma;
+            double total = 0.0, acc = 0.0;
+            for (size_t i = 0; i < take.size(); ++i)
+                if (s->order[i]->form == form)
+                    for (const Item &it : take[i]) total += it.cost;
+            int *b = qb + kind * (kXcds + 1), q_ix = 1;
+            b[0] = 0;
+            for (size_t i = 0; i < take.size(); ++i) {
+                if (s->order[i]->form != form) continue;
+                for (const Item &it : take[i]) {
+                    while (q_ix < kXcds && acc >= total * q_ix / kXcds) b[q_ix++] = k - k0[kind];
+                    fill_persistent_item(P + s->off_items + ib * k, s->order[i]->slot, it.kb, it.cg);
+                    acc += it.cost;
+                    ++k;
+                }
+            }
+            while (q_ix <= kXcds) b[q_ix++] = k - k0[kind];
+            k0[kind + 1] = k;
+        }
         for (size_t i = 0; i < take.size(); ++i) {
             const SReq *q = s->order[i];
-            if (q->split) {
-                std::vector<SplitTile> tiles;
-                for (const Item &it : take[i]) tiles.push_back({q->slot, it.kb, it.cg, it.chunks, it.cost});
-                split.add(split_shape(q->g), tiles);
-            } else {
-                for (const Item &it : take[i]) plain += it.cost;
-            }
+            if (q->form != DirectForm::split) continue;
+            std::vector<SplitTile> tiles;
+            for (const Item &it : take[i]) tiles.push_back({q->slot, it.kb, it.cg, it.chunks, it.cost});
+            split.add(split_shape(q->g), tiles);
         }
-        for (size_t i = 0; i < take.size(); ++i) {
-            if (s->order[i]->split) continue;
-            for (const Item &it : take[i]) {
-                while (q_ix < kXcds && acc >= plain * q_ix / kXcds) qb[q_ix++] = k;
-                fill_persistent_item(P + s->off_items + ib * k, s->order[i]->slot, it.kb, it.cg);
-                acc += it.cost;
-                ++k;
-            }
-        }
-        while (q_ix <= kXcds) qb[q_ix++] = k;
         SplitItems split_n;
         const std::vector<unsigned char> sitems = split.items(&split_n);
         const size_t off_split = s->off_items + ib * static_cast<size_t>(k);
@@ -478,7 +484,7 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
             }
             Workspace wp = ws;
             if (q->mode != 0) wp.zcol = nullptr;   // no a operand planes needed
-            e = q->split ? launch_phases_split(q->g, nullptr, &hdr_dev[q->slot].seed, 1, wp,
+            e = q->mode == 0 && q->form == DirectForm::split ? launch_phases_split(q->g, nullptr, &hdr_dev[q->slot].seed, 1, wp,
                                                static_cast<const double *>(q->r.plan->lr.p), st)
                          : launch_phases(q->g, s->cfg.precision, nullptr, &hdr_dev[q->slot].seed, 1, wp,
                                          static_cast<const double *>(q->r.plan->lr.p), st);
@@ -503,12 +509,14 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
                                            static_cast<unsigned *>(s->split_ctr[c].p), st);
             if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
         }
-        if (k > 0) {
+        for (int kind = 0; kind < 2; ++kind) {
+            if (k0[kind + 1] == k0[kind]) continue;
             char *D = static_cast<char *>(s->dev_stage[c].p);
-            e = launch_pairsum_persistent(s->cfg.precision, s->R, D + s->off_req, D + s->off_items,
-                                          reinterpret_cast<const int *>(D + s->off_q),
-                                          static_cast<int *>(s->qnext[c].p), s->n_cu * s->blocks_per_cu, st, s->mfma,
-                                          s->mfma_shape);
+            e = launch_pairsum_persistent(s->cfg.precision, s->R, D + s->off_req, D + s->off_items + ib * k0[kind],
+                                          reinterpret_cast<const int *>(D + s->off_q) + kind * (kXcds + 1),
+                                          static_cast<int *>(s->qnext[c].p) + kind * kXcds,
+                                          s->n_cu * (kind == 1 ? kMfmaBlocksPerCu : s->blocks_per_cu), st, kind == 1,
+                                          s->mfma ? s->mfma_shape : 0);
             if (e != hipSuccess) return dev_err(e, "persistent pair-sum kernel");
         }
         if ((e = hipEventRecord(s->ev_pairsum[c], st)) != hipSuccess) return dev_err(e, "hipEventRecord");

@@ -216,9 +216,11 @@ __device__ __forceinline__ uint4v load16(brsrc r, unsigned voff, unsigned soff)
     __builtin_memcpy(&u, &v, sizeof u);
     return u;
 }
+constexpr int kCoherent = 16;   // sc1: agent scope
+template <int AUX = 0>
 __device__ __forceinline__ float2v load8(brsrc r, unsigned voff, unsigned soff)
 {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), 0);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), AUX);
     float2v f;
     __builtin_memcpy(&f, &v, sizeof f);
     return f;
@@ -226,11 +228,13 @@ __device__ __forceinline__ float2v load8(brsrc r, unsigned voff, unsigned soff)
 __device__ __forceinline__ void store8(brsrc r, unsigned voff, float2v f)
 {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, f), r, static_cast<int>(voff), 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, f), r, static_cast<int>(voff), 0, kCoherent);
 }
 #else
 __device__ inline void store8(brsrc, unsigned, float2v) {}
 __device__ inline uint4v load16(brsrc, unsigned, unsigned) { return uint4v{}; }
+constexpr int kCoherent = 0;
+template <int AUX = 0>
 __device__ inline float2v load8(brsrc, unsigned, unsigned) { return float2v{}; }
 #endif
 
@@ -498,13 +502,8 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
 
     // commit: add to the sums of the chunks before this one
     if (chunk > 0) {
-        if (tid == 0) {
-            while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                   static_cast<unsigned>(chunk))
-                __builtin_amdgcn_s_sleep(8);
-        }
+        if (tid == 0) wait_count(done, static_cast<unsigned>(chunk));
         __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     // (lines outside the grid get an offset past the buffer: they load zero and are not stored)
     const brsrc tr = make_brsrc(tout, static_cast<unsigned>(g.nk) * static_cast<unsigned>(g.nc) * 8u);
@@ -519,7 +518,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) old[m][c][e] = chunk > 0 ? load8(tr, offset(m, c, e), 0u) : float2v{0.0f, 0.0f};
+            for (int e = 0; e < 4; ++e) old[m][c][e] = chunk > 0 ? load8<kCoherent>(tr, offset(m, c, e), 0u) : float2v{0.0f, 0.0f};
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -528,10 +527,9 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
             for (int e = 0; e < 4; ++e)
                 store8(tr, offset(m, c, e), float2v{__builtin_fmaf(tre[m][c][e], kSplitUnscale, old[m][c][e].x),
                                                     __builtin_fmaf(tim[m][c][e], kSplitUnscale, old[m][c][e].y)});
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    wait_stores();
     __syncthreads();
-    if (tid == 0)
-        __hip_atomic_store(done, static_cast<unsigned>(chunk + 1), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) set_count(done, static_cast<unsigned>(chunk + 1));
 }
 
 // Row waves of a tile: the fewest that hold the grid's rows (64, 128, 256),
