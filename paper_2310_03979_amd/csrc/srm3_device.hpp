@@ -6,6 +6,25 @@
 
 namespace srm3 {
 
+// Read-only data that does not change while a kernel runs, in the constant
+// address space: uniform loads through such a pointer become scalar loads even
+// where the kernel stores elsewhere earlier (the persistent loop).
+// (The host pass of the compiler only parses kernel bodies; it sees plain
+// pointers.)
+#if defined(__HIP_DEVICE_COMPILE__)
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T *;
+#else
+template <typename T>
+using cptr = const T *;
+#endif
+
+template <typename T>
+__device__ __forceinline__ cptr<T> as_const(const T *p)
+{
+    return (cptr<T>)p;
+}
+
 // A pointer that every lane of the wave holds, taken from the first lane so
 // that address arithmetic on it stays scalar.
 template <typename T>
@@ -48,6 +67,44 @@ struct brsrc {
     const void *p;
 };
 __device__ inline brsrc make_brsrc(const void *p, unsigned) { return brsrc{p}; }
+#endif
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// (The loaded vector is copied out whole: extracting its lanes one by one has
+// been folded by the compiler into a single-dword load.)
+__device__ __forceinline__ float2 bload(brsrc r, unsigned voff, unsigned soff, float)
+{
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), 0);
+    static_assert(sizeof(v) == sizeof(float2), "b64 load is two floats");
+    float2 f;
+    __builtin_memcpy(&f, &v, sizeof(f));
+    return f;
+}
+__device__ __forceinline__ double2 bload(brsrc r, unsigned voff, unsigned soff, double)
+{
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(voff), static_cast<int>(soff), 0);
+    static_assert(sizeof(v) == sizeof(double2), "b128 load is two doubles");
+    double2 d;
+    __builtin_memcpy(&d, &v, sizeof(d));
+    return d;
+}
+__device__ __forceinline__ float bload32(brsrc r, unsigned voff, unsigned soff)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, static_cast<int>(voff),
+                                                                          static_cast<int>(soff), 0));
+}
+__device__ __forceinline__ double bload64(brsrc r, unsigned voff, unsigned soff)
+{
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), 0);
+    double d;
+    __builtin_memcpy(&d, &v, sizeof(d));
+    return d;
+}
+#else
+__device__ inline float2 bload(brsrc, unsigned, unsigned, float) { return float2{}; }
+__device__ inline double2 bload(brsrc, unsigned, unsigned, double) { return double2{}; }
+__device__ inline float bload32(brsrc, unsigned, unsigned) { return 0.0f; }
+__device__ inline double bload64(brsrc, unsigned, unsigned) { return 0.0; }
 #endif
 
 // ---------------------------------------------------------------------------

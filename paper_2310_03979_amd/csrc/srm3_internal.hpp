@@ -310,6 +310,11 @@ size_t kfft_workspace_bytes(const Geometry &g, const KfftGeom &k, int precision,
 KfftWorkspace carve_kfft(const Geometry &g, const KfftGeom &k, int precision, int batch, void *base);
 bool kfft_supported(const Geometry &g, const KfftGeom &k, int precision, std::string *why);
 hipError_t launch_wsh(int precision, const void *wt, const Geometry &g, const KfftGeom &k, void *wh, hipStream_t st);
+// Weighted frequency autoconvolution Y of the kappa-DFT rows Z.  The sheared
+// weight table has at least kYpairChunk + 2 zero rows after its 2 W - 1.
+constexpr int kYpairChunk = 32;
+hipError_t launch_ypair(int precision, const Geometry &g, const KfftGeom &k, const void *Z, void *Y, const void *wh,
+                        int batch, hipStream_t st);
 // tw: e^{+2 pi i n / M}, n < M
 hipError_t launch_kfft_pairsum(int precision, const Geometry &g, const KfftGeom &k, const KfftTables &t, int batch,
                                const Workspace &ws, const KfftWorkspace &kw, hipStream_t st);

@@ -45,68 +45,12 @@ __device__ __forceinline__ void b_ops(const T2 &v, T &bsum, T &bim, T &bre)
     bre = v.x;
 }
 
-// Read-only data that does not change while a kernel runs, in the constant
-// address space: uniform loads through such a pointer become scalar loads even
-// where the kernel stores elsewhere earlier (the persistent loop).
-// (The host pass of the compiler only parses kernel bodies; it sees plain
-// pointers.)
-#if defined(__HIP_DEVICE_COMPILE__)
-template <typename T>
-using cptr = const __attribute__((address_space(4))) T *;
-#else
-template <typename T>
-using cptr = const T *;
-#endif
-
-template <typename T>
-__device__ __forceinline__ cptr<T> as_const(const T *p)
-{
-    return (cptr<T>)p;
-}
-
 template <typename T>
 __device__ __forceinline__ gptr<T> as_global(const T *p)
 {
     return (gptr<T>)p;
 }
 
-#if defined(__HIP_DEVICE_COMPILE__)
-// (The loaded vector is copied out whole: extracting its lanes one by one has
-// been folded by the compiler into a single-dword load.)
-__device__ __forceinline__ float2 bload(brsrc r, unsigned voff, unsigned soff, float)
-{
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), 0);
-    static_assert(sizeof(v) == sizeof(float2), "b64 load is two floats");
-    float2 f;
-    __builtin_memcpy(&f, &v, sizeof(f));
-    return f;
-}
-__device__ __forceinline__ double2 bload(brsrc r, unsigned voff, unsigned soff, double)
-{
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(voff), static_cast<int>(soff), 0);
-    static_assert(sizeof(v) == sizeof(double2), "b128 load is two doubles");
-    double2 d;
-    __builtin_memcpy(&d, &v, sizeof(d));
-    return d;
-}
-__device__ __forceinline__ float bload32(brsrc r, unsigned voff, unsigned soff)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, static_cast<int>(voff),
-                                                                          static_cast<int>(soff), 0));
-}
-__device__ __forceinline__ double bload64(brsrc r, unsigned voff, unsigned soff)
-{
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<int>(voff), static_cast<int>(soff), 0);
-    double d;
-    __builtin_memcpy(&d, &v, sizeof(d));
-    return d;
-}
-#else
-__device__ inline float2 bload(brsrc, unsigned, unsigned, float) { return float2{}; }
-__device__ inline double2 bload(brsrc, unsigned, unsigned, double) { return double2{}; }
-__device__ inline float bload32(brsrc, unsigned, unsigned) { return 0.0f; }
-__device__ inline double bload64(brsrc, unsigned, unsigned) { return 0.0; }
-#endif
 
 // Layout of the a operand (re, re + im, im - re) of support column ic, row kk:
 // FP32 keeps three kappa-contiguous planes (a block's rows load as wide scalar
@@ -2196,149 +2140,6 @@ __global__ __launch_bounds__(256) void wsh_kernel(const typename vec<T>::v2 *__r
     wh[idx] = v;
 }
 
-struct YpairArgs {
-    const void *Z;      // [B][M][ncw] phase DFTs along kappa
-    void *Y;            // [B][M][nca]
-    const void *wh;     // [wh_rows][nca] sheared half table, zero rows after row ncw - 1
-    int M, W, nca, kw0;
-    int batch, n_qtiles, n_ctiles, per_xcd;
-    int one_sided;      // partners i_w <= k_omega only (both partners >= 0)
-};
-
-// Staged form of the frequency autoconvolution.  A wave owns 64 consecutive
-// output columns (one per lane) and R DFT rows q, and walks the partner
-// frequencies i_w in chunks of C steps.  The b operand Z[q][kw - i_w] of lane
-// l at step i_w is element e = e0 + l - i_w of row q, so a chunk reads a
-// window of 64 + C - 1 elements per row; the window and the chunk's a
-// operands Z[q][i_w] (the same for all lanes) are staged in the wave's own
-// slice of LDS with coalesced global loads -- no barrier: the wave alone
-// writes and reads its slice.  The weight row W_h[i_w][.] is read from global
-// memory once per step for all R rows, two steps ahead.  Steps past the last
-// partner meet zero weights (zero rows after the table, or pairs outside the
-// support).  Per term: t = a b (4 ops), acc += w t (4 FMAs).
-constexpr int kY2Rows = 8;      // DFT rows per wave
-constexpr int kY2Chunk = 32;    // steps per staged window
-constexpr int kY2Unroll = 4;
-
-template <typename T, int R, int C>
-__global__ __launch_bounds__(256) void ypair2_kernel(YpairArgs a)
-{
-    using T2 = typename vec<T>::v2;
-    constexpr int LW = 64 + C;   // staged elements per row (64 + C - 1 used)
-    static_assert((R * LW) % 64 == 0 && (C * R) % 64 == 0 && C % kY2Unroll == 0, "staging shape");
-    extern __shared__ unsigned char smem_raw[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    T2 *ldsb = reinterpret_cast<T2 *>(smem_raw) + wave * (R * LW + C * R);
-    T2 *ldsa = ldsb + R * LW;
-    // a block: one column tile, kWavesPerBlock consecutive q tiles (one per
-    // wave), so that its waves read the same weight rows at about the same time
-    const int bid = blockIdx.x;
-    const int work = (bid % kNumXcd) * a.per_xcd + bid / kNumXcd;
-    const int n_qgroups = (a.n_qtiles + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int per_b = n_qgroups * a.n_ctiles;
-    if (work >= a.batch * per_b) return;
-    const int b = work / per_b;
-    const int rem = work - b * per_b;
-    const int qg = rem / a.n_ctiles;
-    const int ct = rem - qg * a.n_ctiles;
-    const int qt = qg * kWavesPerBlock + wave;
-    if (qt >= a.n_qtiles) return;
-    const int cc0 = ct * 64;
-    const int W = a.W, ncw = 2 * W - 1, q0 = qt * R;
-    const T2 *Zb = static_cast<const T2 *>(a.Z) + static_cast<long>(b) * a.M * ncw;
-    const int kw_lo = a.kw0 + cc0;
-    const int kw_hi = a.kw0 + min(cc0 + 64, a.nca) - 1;
-    const int iw_lo = max(-W + 1, (kw_lo + 1) >> 1);
-    const int iw_hi = min(W - 1, a.one_sided ? kw_hi : kw_hi + W - 1);
-    const int nchunk = __builtin_amdgcn_readfirstlane(iw_hi >= iw_lo ? (iw_hi - iw_lo + C) / C : 0);
-    const gptr<T2> wcol = as_global(static_cast<const T2 *>(a.wh)) + cc0 + lane;
-    const long wstride = a.nca;
-
-    T accr[R], acci[R], sumr[R], sumi[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) accr[r] = acci[r] = sumr[r] = sumi[r] = T(0);
-
-    for (int ch = 0; ch < nchunk; ++ch) {
-        const int iwc = iw_lo + ch * C;
-        // b window: lane l at chunk step s reads index l + C - 1 - s of row r
-        const int e_lo = kw_lo + W - 1 - (iwc + C - 1);
-#pragma unroll
-        for (int i = 0; i < R * LW / 64; ++i) {
-            const int idx = i * 64 + lane;
-            const int r = idx / LW, x = idx - r * LW;
-            const int e = e_lo + x;
-            T2 v;
-            v.x = T(0);
-            v.y = T(0);
-            if (e >= 0 && e < ncw) v = Zb[static_cast<long>(min(q0 + r, a.M - 1)) * ncw + e];
-            ldsb[r * LW + x] = v;
-        }
-        // a operands of the chunk, [s][r]
-#pragma unroll
-        for (int i = 0; i < C * R / 64; ++i) {
-            const int idx = i * 64 + lane;
-            const int st = idx / R, r = idx - st * R;
-            const int ic = iwc + st + W - 1;
-            T2 v;
-            v.x = T(0);
-            v.y = T(0);
-            if (ic < ncw) v = Zb[static_cast<long>(min(q0 + r, a.M - 1)) * ncw + ic];
-            ldsa[st * R + r] = v;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int ic0 = iwc + W - 1;
-        T2 w0 = wcol[static_cast<long>(ic0) * wstride];
-        T2 w1 = wcol[static_cast<long>(ic0 + 1) * wstride];
-        for (int s0 = 0; s0 < C; s0 += kY2Unroll) {
-#pragma unroll
-            for (int u = 0; u < kY2Unroll; ++u) {
-                const int s = s0 + u;
-                const T2 w2 = wcol[static_cast<long>(ic0 + s + 2) * wstride];
-                const int x = lane + C - 1 - s;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const T2 av = ldsa[s * R + r];
-                    const T2 bv = ldsb[r * LW + x];
-                    const T tr = fma_(av.x, bv.x, -av.y * bv.y);
-                    const T ti = fma_(av.x, bv.y, av.y * bv.x);
-                    accr[r] = fma_(w0.x, tr, accr[r]);
-                    accr[r] = fma_(-w0.y, ti, accr[r]);
-                    acci[r] = fma_(w0.x, ti, acci[r]);
-                    acci[r] = fma_(w0.y, tr, acci[r]);
-                }
-                w0 = w1;
-                w1 = w2;
-            }
-        }
-        // the slice is rewritten by the next chunk only after these reads
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (ch & 1) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                sumr[r] += accr[r];
-                sumi[r] += acci[r];
-                accr[r] = acci[r] = T(0);
-            }
-        }
-    }
-    T2 *Y = static_cast<T2 *>(a.Y) + static_cast<long>(b) * a.M * a.nca;
-    const int cc = cc0 + lane;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (cc < a.nca && q0 + r < a.M) {
-            T2 v;
-            v.x = sumr[r] + accr[r];
-            v.y = sumi[r] + acci[r];
-            Y[static_cast<long>(q0 + r) * a.nca + cc] = v;
-        }
-    }
-}
-
 // Pair weight table W[i][j] = sqrt(b2_raw(i, j)) exp(i beta(i, j)) over the
 // support |i_w|, |j_w| < W (index i_w + W - 1), computed in FP64 and stored in
 // the path precision.  b2_raw = g2[i] g2[j] (separable) or b2[i][j] (dense);
@@ -2941,7 +2742,7 @@ KfftGeom kfft_geometry(const Geometry &g, bool one_sided)
     // zero rows after the table: the weight rows read up to C + 1 steps past
     // the last partner, and the ragged last column tile (< 64 columns past a
     // row's end)
-    k.wh_rows = g.ncw + kY2Chunk + 2 + (64 + k.nca - 1) / k.nca;
+    k.wh_rows = g.ncw + kYpairChunk + 2 + (64 + k.nca - 1) / k.nca;
     return k;
 }
 
@@ -3054,30 +2855,7 @@ static hipError_t kfft_pairsum_t(const Geometry &g, const KfftGeom &k, const Kff
         }
     } else {
     // weighted frequency autoconvolution per kappa frequency q
-    YpairArgs y{};
-    y.Z = kw.Z;
-    y.Y = kw.Y;
-    y.wh = wh;
-    y.M = k.M;
-    y.W = g.W;
-    y.nca = k.nca;
-    y.kw0 = k.kw0;
-    y.batch = batch;
-    y.one_sided = k.one_sided;
-    if (k.M == 1) {
-        // one kappa line: the realizations are the rows ([B][1][.] == [B][.])
-        y.M = batch;
-        y.batch = 1;
-    }
-    y.n_qtiles = (y.M + kY2Rows - 1) / kY2Rows;
-    y.n_ctiles = (k.nca + 63) / 64;
-    const long blocks = static_cast<long>(y.batch) * ((y.n_qtiles + kWavesPerBlock - 1) / kWavesPerBlock) * y.n_ctiles;
-    y.per_xcd = static_cast<int>((blocks + kNumXcd - 1) / kNumXcd);
-    const size_t lds = static_cast<size_t>(kWavesPerBlock) * (kY2Rows * (64 + kY2Chunk) + kY2Chunk * kY2Rows) *
-                       sizeof(T2);
-    ypair2_kernel<T, kY2Rows, kY2Chunk><<<dim3(static_cast<unsigned>(static_cast<long>(y.per_xcd) * kNumXcd)),
-                                         64 * kWavesPerBlock, lds, st>>>(y);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_ypair(sizeof(T) == 8 ? SRM3_FP64 : SRM3_FP32, g, k, kw.Z, kw.Y, wh, batch, st)) != hipSuccess) return e;
     }
     for (int b0 = 0; b0 < batch; b0 += 65535) {
         const int nb = std::min(65535, batch - b0);
