@@ -181,18 +181,6 @@ std::vector<double> pass_twiddles(int N)
     return v;
 }
 
-// exp(+2 pi i n / N), n < N, interleaved
-std::vector<double> twiddles(int N)
-{
-    std::vector<double> v(2 * static_cast<size_t>(N));
-    for (int n = 0; n < N; ++n) {
-        const long double a = 2.0L * 3.14159265358979323846264338327950288L * n / N;
-        v[2 * n] = static_cast<double>(cosl(a));
-        v[2 * n + 1] = static_cast<double>(sinl(a));
-    }
-    return v;
-}
-
 srm3_status event_pair(srm3_plan_t p, int kernel, hipStream_t st, bool begin)
 {
     if (!p->prof) return SRM3_OK;
@@ -880,7 +868,7 @@ srm3_status srm3_plan_set_algorithm(srm3_plan_t plan, int32_t algorithm, void *h
         std::vector<double> g(plan->g2_host.size());
         for (size_t i = 0; i < g.size(); ++i) g[i] = std::sqrt(plan->g2_host[i]);
         if ((s = upload(plan->gw, g, plan->precision, st))) return s;
-        if ((s = upload(plan->tw_l, twiddles(L), plan->precision, st))) return s;
+        if ((s = upload(plan->tw_l, pass_twiddles(L), plan->precision, st))) return s;
     } else {
         const size_t e2 = plan->precision == SRM3_FP64 ? 16 : 8;
         hipError_t e = plan->wsh.alloc(static_cast<size_t>(k.wh_rows) * k.nca * e2);
@@ -888,7 +876,7 @@ srm3_status srm3_plan_set_algorithm(srm3_plan_t plan, int32_t algorithm, void *h
         if ((e = launch_wsh(plan->precision, plan->wtab.p, plan->g, k, plan->wsh.p, st)) != hipSuccess)
             return dev_err(e, "sheared weight table kernel");
     }
-    if ((s = upload(plan->tw_k, twiddles(k.M), plan->precision, st))) return s;
+    if ((s = upload(plan->tw_k, pass_twiddles(k.M), plan->precision, st))) return s;
     plan->kg = k;
     plan->kws_batch = 0;
     plan->algo = algorithm;

@@ -1061,12 +1061,6 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *p, size_t n, ui
     for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// ---------------------------------------------------------------------------
-// Stockham inverse DFT in LDS (radix-4 stages, one radix-2 stage when log2 N
-// is odd), for `nbatch` transforms of length N stored `ld` apart.  Every stage
-// reads its inputs into registers, synchronises, then writes the permuted
-// outputs (natural order at the end).  tw[n] = exp(+2 pi i n / N).
-// ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ typename vec<T>::v2 cmul(typename vec<T>::v2 a, typename vec<T>::v2 b)
 {
@@ -1074,84 +1068,6 @@ __device__ __forceinline__ typename vec<T>::v2 cmul(typename vec<T>::v2 a, typen
     r.x = a.x * b.x - a.y * b.y;
     r.y = fma_(a.x, b.y, a.y * b.x);
     return r;
-}
-
-template <typename T, int MAXB>
-__device__ void fft_lds(typename vec<T>::v2 *buf, int N, int ld, int nbatch,
-                        const typename vec<T>::v2 *__restrict__ tw)
-{
-    using T2 = typename vec<T>::v2;
-    const int nthr = blockDim.x, tid = threadIdx.x;
-    int Ns = 1;
-    const int q4 = N >> 2;
-    while (Ns * 4 <= N) {
-        const int total = nbatch * q4;
-        const int s = N / (4 * Ns);
-        T2 y[MAXB][4];
-        int dst[MAXB];
-#pragma unroll
-        for (int i = 0; i < MAXB; ++i) {
-            const int q = tid + i * nthr;
-            dst[i] = -1;
-            if (q < total) {
-                const int f = q / q4, j = q - f * q4;
-                T2 *B = buf + static_cast<long>(f) * ld;
-                const int k = j & (Ns - 1);
-                const T2 x0 = B[j];
-                const T2 x1 = cmul<T>(B[j + q4], tw[k * s]);
-                const T2 x2 = cmul<T>(B[j + 2 * q4], tw[2 * k * s]);
-                const T2 x3 = cmul<T>(B[j + 3 * q4], tw[3 * k * s]);
-                const T ar = x0.x + x2.x, ai = x0.y + x2.y;
-                const T br = x0.x - x2.x, bi = x0.y - x2.y;
-                const T cr = x1.x + x3.x, ci = x1.y + x3.y;
-                const T dr = x1.x - x3.x, di = x1.y - x3.y;
-                y[i][0].x = ar + cr; y[i][0].y = ai + ci;
-                y[i][1].x = br - di; y[i][1].y = bi + dr;   // x0 + i x1 - x2 - i x3
-                y[i][2].x = ar - cr; y[i][2].y = ai - ci;
-                y[i][3].x = br + di; y[i][3].y = bi - dr;   // x0 - i x1 - x2 + i x3
-                dst[i] = f * ld + (j / Ns) * 4 * Ns + k;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MAXB; ++i) {
-            if (dst[i] >= 0) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) buf[dst[i] + r * Ns] = y[i][r];
-            }
-        }
-        __syncthreads();
-        Ns *= 4;
-    }
-    if (Ns < N) {   // one radix-2 stage, Ns == N / 2
-        const int q2 = N >> 1;
-        const int total = nbatch * q2;
-        T2 y[2 * MAXB][2];
-        int dst[2 * MAXB];
-#pragma unroll
-        for (int i = 0; i < 2 * MAXB; ++i) {
-            const int q = tid + i * nthr;
-            dst[i] = -1;
-            if (q < total) {
-                const int f = q / q2, j = q - f * q2;
-                T2 *B = buf + static_cast<long>(f) * ld;
-                const T2 x0 = B[j];
-                const T2 x1 = cmul<T>(B[j + q2], tw[j]);
-                y[i][0].x = x0.x + x1.x; y[i][0].y = x0.y + x1.y;
-                y[i][1].x = x0.x - x1.x; y[i][1].y = x0.y - x1.y;
-                dst[i] = f * ld + j;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 2 * MAXB; ++i) {
-            if (dst[i] >= 0) {
-                buf[dst[i]] = y[i][0];
-                buf[dst[i] + q2] = y[i][1];
-            }
-        }
-        __syncthreads();
-    }
 }
 
 // Amplitudes of Eq. pure and the pair term, per line and realization, in
@@ -1824,12 +1740,18 @@ __global__ __launch_bounds__(sizeof(T) == 8 ? 512 : 1024) void xfft_kernel(XfftA
 // terms against N_kappa^2 (2W - 1)^2 / 4 in the direct form.
 // ---------------------------------------------------------------------------
 
-// Column DFTs over the rows of a row-major array, one block per tc columns:
+// Column DFTs over the rows of a row-major array, one block per np columns:
 // rows [0, in_rows) of columns col0 .. col0 + ncols - 1 are read (the rest of
 // the N inputs are zero), transformed and rows [0, out_rows) are written,
-// scaled, to columns ocol0 + c of the output.  `tw` is e^{+2 pi i n/N}; the
-// forward transform (e^{-2 pi i}) conjugates the input and the output of the
-// inverse one.
+// scaled, to columns ocol0 + c of the output.  The forward transform
+// (e^{-2 pi i}) conjugates the input and the output of the inverse one.  The
+// register-blocked FFT with the columns on consecutive lanes: rows are read
+// straight into the first pass and written from the last.  Bound by memory;
+// 64 KB of LDS, so that two blocks share a CU and one loads while the other
+// transforms.  Against radix-4 stages in 32 KB of LDS with a pass over LDS for
+// the loads and one for the stores: 256x1024 lines, 64 realizations, FP32, a
+// call of the kappa-DFT form 14.83 -> 14.60 ms (its two column transforms were
+// 0.88 ms); one of 100x333 lines, 3 realizations, 186 -> 123 us.
 struct ColfftArgs {
     const void *in;
     long in_bstride;    // elements between realizations
@@ -1837,46 +1759,43 @@ struct ColfftArgs {
     void *out;
     long out_bstride;
     int out_ld, out_rows, ocol0;
-    int ncols, N, tc;
+    int ncols, N, np;
+    FftSched sched;     // length N
     int forward;
-    const void *tw;
+    const void *tw;     // pass twiddles of N
     double scale;
-    int tw_lds;         // 1: the twiddles are copied to LDS after the tile
 };
 
-template <typename T, int MAXB>
-__global__ __launch_bounds__(256) void colfft_kernel(ColfftArgs a)
+template <typename T>
+__global__ __launch_bounds__(sizeof(T) == 8 ? 256 : 512) void colfft_kernel(ColfftArgs a)
 {
     using T2 = typename vec<T>::v2;
     extern __shared__ unsigned char smem_raw[];
     T2 *buf = reinterpret_cast<T2 *>(smem_raw);
-    const int b = blockIdx.y;
-    const int c0 = blockIdx.x * a.tc;
-    const int tc = min(a.tc, a.ncols - c0);
-    const T2 *in = static_cast<const T2 *>(a.in) + b * a.in_bstride;
-    for (int n = threadIdx.x; n < a.tc * a.N; n += blockDim.x) {
-        const int row = n / a.tc, col = n - row * a.tc;
+    const int c0 = blockIdx.x * a.np;
+    const int nc = min(a.np, a.ncols - c0), in_rows = a.in_rows, out_rows = a.out_rows;
+    const long in_ld = a.in_ld, out_ld = a.out_ld;
+    const T2 *in = static_cast<const T2 *>(a.in) + blockIdx.y * a.in_bstride + a.col0 + c0;
+    T2 *out = static_cast<T2 *>(a.out) + blockIdx.y * a.out_bstride + a.ocol0 + c0;
+    const T sgn = a.forward ? T(-1) : T(1);
+    const T sc = static_cast<T>(a.scale), sci = sgn * sc;
+    auto load = [=](int f, int n) -> T2 {
         T2 v;
         v.x = T(0);
         v.y = T(0);
-        if (row < a.in_rows && col < tc) v = in[static_cast<long>(row) * a.in_ld + a.col0 + c0 + col];
-        if (a.forward) v.y = -v.y;
-        buf[col * a.N + row] = v;
-    }
-    T2 *twl = buf + a.tc * a.N;
-    if (a.tw_lds)
-        for (int n = threadIdx.x; n < a.N; n += blockDim.x) twl[n] = static_cast<const T2 *>(a.tw)[n];
-    __syncthreads();
-    fft_lds<T, MAXB>(buf, a.N, a.N, a.tc, a.tw_lds ? twl : static_cast<const T2 *>(a.tw));
-    T2 *out = static_cast<T2 *>(a.out) + b * a.out_bstride;
-    const T sc = static_cast<T>(a.scale);
-    for (int n = threadIdx.x; n < a.out_rows * tc; n += blockDim.x) {
-        const int row = n / tc, col = n - row * tc;
-        T2 v = buf[col * a.N + row];
+        if (n < in_rows && f < nc) {
+            v = in[n * in_ld + f];
+            v.y *= sgn;
+        }
+        return v;
+    };
+    auto store = [=](int f, int n, T2 v) {
+        if (n >= out_rows || f >= nc) return;
         v.x *= sc;
-        v.y *= a.forward ? -sc : sc;
-        out[static_cast<long>(row) * a.out_ld + a.ocol0 + c0 + col] = v;
-    }
+        v.y *= sci;
+        out[n * out_ld + f] = v;
+    };
+    fft_block<T, true, false>(buf, a.sched, a.np, static_cast<const T2 *>(a.tw), load, store);
 }
 
 // Zero the pair sums of the output columns that no frequency pair reaches.
@@ -2062,55 +1981,59 @@ struct RowconvArgs {
     const void *Z;      // [rows][2W - 1] phase DFTs along kappa
     void *Y;            // [rows][nca]
     const void *gw;     // [2W - 1] g = sqrt(g2), path precision
-    const void *tw;     // [L] exp(+2 pi i n / L)
-    int W, nca, kw0, L;
-    int tw_lds;         // 1: the twiddles are copied to LDS after the row
+    const void *tw;     // pass twiddles of L
+    int W, nca, kw0, L, np;
+    FftSched sched;     // length L
+    long rows;
 };
 
-template <typename T, int MAXB>
-__global__ __launch_bounds__(1024) void rowconv_kernel(RowconvArgs a)
+// The register-blocked FFT: 256x128 lines, 64 realizations, FP32, a call of the
+// 2-D FFT form 494 -> 418 us together with the column transforms (radix-4
+// stages in LDS, one row a block, before); FP64 983 -> 777 us; one realization
+// 86 -> 74 us.
+//
+// np rows per block: the forward transform of conj(g z) from global memory
+// straight into its first pass, its last pass leaves the squares in LDS, and
+// the second transform writes the output columns from its last pass.
+template <typename T>
+__global__ __launch_bounds__(sizeof(T) == 8 ? 512 : 1024) void rowconv_kernel(RowconvArgs a)
 {
     using T2 = typename vec<T>::v2;
     extern __shared__ unsigned char smem_raw[];
     T2 *buf = reinterpret_cast<T2 *>(smem_raw);
-    const int ncw = 2 * a.W - 1;
-    const long row = blockIdx.x;
-    const T2 *z = static_cast<const T2 *>(a.Z) + row * ncw;
+    const int ncw = 2 * a.W - 1, nca = a.nca, L = a.L, first = a.kw0 + 2 * a.W - 2;
+    const long row0 = static_cast<long>(blockIdx.x) * a.np, rows = a.rows;
+    const T2 *z = static_cast<const T2 *>(a.Z);
     const T *gw = static_cast<const T *>(a.gw);
-    for (int n = threadIdx.x; n < a.L; n += blockDim.x) {
+    auto load = [=](int f, int n) -> T2 {
         T2 v;
         v.x = T(0);
         v.y = T(0);
-        if (n < ncw) {
-            const T2 x = z[n];
+        if (n < ncw && row0 + f < rows) {
+            const T2 x = z[(row0 + f) * ncw + n];
             v.x = gw[n] * x.x;
             v.y = -gw[n] * x.y;
         }
-        buf[n] = v;
-    }
-    T2 *twl = buf + a.L;
-    if (a.tw_lds)
-        for (int n = threadIdx.x; n < a.L; n += blockDim.x) twl[n] = static_cast<const T2 *>(a.tw)[n];
-    const T2 *tw = a.tw_lds ? twl : static_cast<const T2 *>(a.tw);
-    __syncthreads();
-    fft_lds<T, MAXB>(buf, a.L, a.L, 1, tw);
-    for (int n = threadIdx.x; n < a.L; n += blockDim.x) {
-        const T2 f = buf[n];
+        return v;
+    };
+    auto square = [=](int f, int n, T2 x) {
         T2 v;
-        v.x = f.x * f.x - f.y * f.y;
-        v.y = T(-2) * f.x * f.y;
-        buf[n] = v;
-    }
+        v.x = x.x * x.x - x.y * x.y;
+        v.y = T(-2) * x.x * x.y;
+        buf[lpad<T>(f * L + n)] = v;
+    };
+    fft_block<T, false, false>(buf, a.sched, a.np, static_cast<const T2 *>(a.tw), load, square);
     __syncthreads();
-    fft_lds<T, MAXB>(buf, a.L, a.L, 1, tw);
-    T2 *y = static_cast<T2 *>(a.Y) + row * a.nca;
-    const T sc = T(1) / static_cast<T>(a.L);
-    for (int cc = threadIdx.x; cc < a.nca; cc += blockDim.x) {
-        T2 v = buf[a.kw0 + cc + 2 * a.W - 2];
+    T2 *y = static_cast<T2 *>(a.Y);
+    const T sc = T(1) / static_cast<T>(L);
+    auto store = [=](int f, int n, T2 v) {
+        const int cc = n - first;
+        if (cc < 0 || cc >= nca || row0 + f >= rows) return;
         v.x *= sc;
         v.y *= sc;
-        y[cc] = v;
-    }
+        y[(row0 + f) * nca + cc] = v;
+    };
+    fft_block<T, false, true>(buf, a.sched, a.np, static_cast<const T2 *>(a.tw), load, store);
 }
 
 // Sheared half table Wh[ic][cc] = f W(i_w, kw - i_w) over the active output
@@ -2198,17 +2121,6 @@ __global__ __launch_bounds__(256) void spectrum_kernel(int nk, int nw, double dk
         v = sw * (a / 3.14159265358979323846264338327950288) / (a * a + kap * kap);
     }
     S[idx] = v;
-}
-
-constexpr int kFftMaxB = 4;
-
-int fft_threads(int butterflies)
-{
-    int t = (butterflies + kFftMaxB - 1) / kFftMaxB;
-    t = ((t + 63) / 64) * 64;
-    if (t < 64) t = 64;
-    if (t > 1024) t = 1024;
-    return t;
 }
 
 }  // namespace
@@ -2788,16 +2700,29 @@ hipError_t launch_wsh(int precision, const void *wt, const Geometry &g, const Kf
     return precision == SRM3_FP64 ? wsh_t<double>(wt, g, k, wh, st) : wsh_t<float>(wt, g, k, wh, st);
 }
 
+// Elements of a block of the column and row transforms: 64 KB of LDS (a length
+// above it takes a block of its own).
+template <typename T>
+constexpr int small_block_elems()
+{
+    return sizeof(T) == 8 ? 4096 : 8192;
+}
+
 template <typename T>
 static hipError_t colfft_t(ColfftArgs a, int batch, hipStream_t st)
 {
     using T2 = typename vec<T>::v2;
-    a.tc = std::max(1, static_cast<int>(32768 / (static_cast<long>(a.N) * sizeof(T2))));
-    const dim3 grid(static_cast<unsigned>((a.ncols + a.tc - 1) / a.tc), static_cast<unsigned>(batch));
-    size_t lds = static_cast<size_t>(a.tc) * a.N * sizeof(T2);
-    a.tw_lds = lds + a.N * sizeof(T2) <= 131072 ? 1 : 0;
-    if (a.tw_lds) lds += a.N * sizeof(T2);
-    colfft_kernel<T, 4><<<grid, 256, lds, st>>>(a);
+    a.sched = fft_schedule(a.N);
+    // columns per block: 64 KB of LDS, at most 512, no more than the columns
+    // need, and fewer (down to rows of 128 bytes) while the grid has under two
+    // blocks for each of the 256 CUs
+    a.np = std::min(512, std::max(1, small_block_elems<T>() / a.N));
+    while (a.np > 1 && a.np / 2 >= a.ncols) a.np /= 2;
+    const int run = 128 / static_cast<int>(sizeof(T2));
+    while (a.np > run && static_cast<long>((a.ncols + a.np - 1) / a.np) * batch < 512) a.np /= 2;
+    const dim3 grid(static_cast<unsigned>((a.ncols + a.np - 1) / a.np), static_cast<unsigned>(batch));
+    const long elems = static_cast<long>(a.np) * a.N;
+    colfft_kernel<T><<<grid, fft_block_threads(elems), static_cast<size_t>(elems) * sizeof(T2), st>>>(a);
     return hipGetLastError();
 }
 
@@ -2840,22 +2765,24 @@ static hipError_t kfft_pairsum_t(const Geometry &g, const KfftGeom &k, const Kff
         r.nca = k.nca;
         r.kw0 = k.kw0;
         r.L = k.L;
-        const long rows = static_cast<long>(batch) * k.M;
-        const int thr = fft_threads(k.L / 2);
-        size_t lds = static_cast<size_t>(k.L) * sizeof(T2);
-        r.tw_lds = 2 * lds <= 131072 ? 1 : 0;
-        if (r.tw_lds) lds *= 2;
-        for (long r0 = 0; r0 < rows; r0 += 1L << 30) {
-            const long nr = std::min(rows - r0, 1L << 30);
-            RowconvArgs rr = r;
-            rr.Z = static_cast<const T2 *>(kw.Z) + r0 * g.ncw;
-            rr.Y = static_cast<T2 *>(kw.Y) + r0 * k.nca;
-            rowconv_kernel<T, kFftMaxB><<<dim3(static_cast<unsigned>(nr)), thr, lds, st>>>(rr);
+        r.rows = static_cast<long>(batch) * k.M;
+        r.sched = fft_schedule(k.L);
+        r.np = std::max(1, small_block_elems<T>() / k.L);
+        while (r.np > 1 && (r.rows + r.np - 1) / r.np < 512) r.np /= 2;
+        const int elems = r.np * k.L;
+        const size_t lds = static_cast<size_t>(fft_lds_elems<T>(elems)) * sizeof(T2);
+        const long per = static_cast<long>(r.np) << 20;   // rows of one launch
+        const long rows = r.rows;
+        for (long r0 = 0; r0 < rows; r0 += per) {
+            r.rows = std::min(rows - r0, per);
+            r.Z = static_cast<const T2 *>(kw.Z) + r0 * g.ncw;
+            r.Y = static_cast<T2 *>(kw.Y) + r0 * k.nca;
+            rowconv_kernel<T><<<dim3(static_cast<unsigned>((r.rows + r.np - 1) / r.np)), fft_block_threads(elems), lds, st>>>(r);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     } else {
-    // weighted frequency autoconvolution per kappa frequency q
-    if ((e = launch_ypair(sizeof(T) == 8 ? SRM3_FP64 : SRM3_FP32, g, k, kw.Z, kw.Y, wh, batch, st)) != hipSuccess) return e;
+        // weighted frequency autoconvolution per kappa frequency q
+        if ((e = launch_ypair(sizeof(T) == 8 ? SRM3_FP64 : SRM3_FP32, g, k, kw.Z, kw.Y, wh, batch, st)) != hipSuccess) return e;
     }
     for (int b0 = 0; b0 < batch; b0 += 65535) {
         const int nb = std::min(65535, batch - b0);
@@ -2921,7 +2848,6 @@ double kfft_terms(const Geometry &g, const KfftGeom &k)
 template <typename T>
 static hipError_t prepare_t()
 {
-    const int lds = 131072;
     // the transforms' padded rows take up to 139 KB (of the 160 KB of a workgroup)
     const void *tk[] = {reinterpret_cast<const void *>(&tfft_kernel<T, 0, true>),
                         reinterpret_cast<const void *>(&tfft_kernel<T, 0, false>),
@@ -2932,11 +2858,11 @@ static hipError_t prepare_t()
     hipError_t e = hipSuccess;
     for (const void *k : tk)
         if ((e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 163840)) != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rowconv_kernel<T, kFftMaxB>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&rowconv_kernel<T>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&colfft_kernel<T, kFftMaxB>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&colfft_kernel<T>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&xfft_kernel<T>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
