@@ -8,7 +8,7 @@ inverse DFT, with the plan (spectrum, bicoherence table) resident on the device.
 Also reported:
 
 * plain   -- the same realizations, one non-batched call per realization
-* vector_pairsum -- the FP32 step with the pair sum on the vector ALUs
+* mfma_fp32_pairsum -- the FP32 step with the pair sum on the FP32 matrix instructions
 * roofline -- the pair-sum kernel (the dominant kernel: on the matrix cores by
               default), timed with HIP events recorded by the library on its
               launch stream during the timed steps
@@ -38,9 +38,31 @@ PEAK_FP32_TFLOPS = 157.3      # MI355X vector FP32 (published)
 PEAK_FP32_MFMA_TFLOPS = 157.3 # MI355X dense FP32 matrix (published)
 PEAK_FP64_TFLOPS = 78.6       # MI355X vector FP64 (published)
 FMA_ISSUE_FP32_TFLOPS = 78.6  # non-packed FP32 FMA issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2 flops x 2.4 GHz
+PEAK_FP16_MFMA_TFLOPS = 2500.0  # MI355X dense FP16 matrix (published)
 PEAK_HBM_GBS = 8000.0
 FLOPS_PER_PAIR_TERM = 14      # complex product z_i z_j (6) x W (6) + accumulate (2)
 MFMA_FLOPS_PER_PAIR_TERM = 6  # the matrix cores' share: three real products (Gauss form), each a multiply-add
+
+SPLIT_FLOPS_PER_PAIR_TERM = 24  # split-FP16 form: a complex product in three FP16 products each, 12 multiply-adds
+SPLIT_MIN_ROWS = 32             # n_kappa from which FP32 plans with the default tile take the split form
+
+
+def split_form(n_kappa, shape=0):
+    """Whether an FP32 pair sum runs the split-FP16 form (both the default
+    algorithm and the matrix cores'; smaller grids and explicit tiles don't)."""
+    return shape == 0 and n_kappa >= SPLIT_MIN_ROWS
+
+
+def pair_roofline(n_kappa, mfma, shape=0):
+    """(bound, flops per pair term, peak TFLOP/s) of the FP32 pair sum."""
+    if split_form(n_kappa, shape):
+        return "mfma", SPLIT_FLOPS_PER_PAIR_TERM, PEAK_FP16_MFMA_TFLOPS
+    if mfma:
+        return "mfma", MFMA_FLOPS_PER_PAIR_TERM, PEAK_FP32_MFMA_TFLOPS
+    return "alu", MFMA_FLOPS_PER_PAIR_TERM, FMA_ISSUE_FP32_TFLOPS
+
+
+SPLIT_LABEL = "matrix cores (split FP16, FP32 sums)"
 
 
 def log(*a):
@@ -433,7 +455,7 @@ def bench_uneven(args, torch, srm3):
     ps_ms = dinfo["pairsum_ms"]
     # both kernels execute 6 flops per pair term (three real products); the
     # vector kernel's ceiling is the non-packed FP32 FMA issue rate
-    achieved = MFMA_FLOPS_PER_PAIR_TERM * terms / (ps_ms * 1e-3) / 1e12
+    achieved = SPLIT_FLOPS_PER_PAIR_TERM * terms / (ps_ms * 1e-3) / 1e12   # every grid has 64 rows or more
     log(f"[bench] batched graph: {dt * 1e3:.1f} ms/step; pair sum {ps_ms:.1f} ms")
     rec_plain = None
     if not args.no_plain:
@@ -468,17 +490,12 @@ def bench_uneven(args, torch, srm3):
         "config": {"workload": f"uneven batch: {len(reqs)} realizations, line grids 2^U{{6..9}} x "
                                f"2^U{{7..12}} (64x128 .. 512x4096), b2 scale U[0.05, 0.3], one "
                                f"persistent launch, autotuned, hipGraph", "global_batch": len(reqs),
-                   "pair_kernel": "matrix cores (FP32 MFMA)" if mfma else "vector ALUs"},
-        "roofline": ({"bound": "mfma", "kernel": "pairsum_persistent_mfma (matrix-core items)",
-                      "achieved": round(achieved, 3), "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                      "frac": round(achieved / PEAK_FP32_MFMA_TFLOPS, 4), "traffic": None,
-                      "flops_per_pair_term": MFMA_FLOPS_PER_PAIR_TERM,
-                      "pair_terms_per_launch": terms, "avg_launch_ms": round(ps_ms, 3)} if mfma else
-                     {"bound": "alu", "kernel": f"pairsum_persistent<float,{dinfo['rows_per_wave']},true>",
-                      "achieved": round(achieved, 3), "peak": FMA_ISSUE_FP32_TFLOPS, "unit": "TFLOP/s",
-                      "frac": round(achieved / FMA_ISSUE_FP32_TFLOPS, 4), "traffic": None,
-                      "flops_per_pair_term": MFMA_FLOPS_PER_PAIR_TERM,
-                      "pair_terms_per_launch": terms, "avg_launch_ms": round(ps_ms, 3)}),
+                   "pair_kernel": SPLIT_LABEL},
+        "roofline": {"bound": "mfma", "kernel": "pairsum_split_kernel (v_mfma_f32_16x16x32_f16, batch items)",
+                     "achieved": round(achieved, 3), "peak": PEAK_FP16_MFMA_TFLOPS, "unit": "TFLOP/s",
+                     "frac": round(achieved / PEAK_FP16_MFMA_TFLOPS, 4), "traffic": None,
+                     "flops_per_pair_term": SPLIT_FLOPS_PER_PAIR_TERM,
+                     "pair_terms_per_launch": terms, "avg_launch_ms": round(ps_ms, 3)},
         "pair_sum_complex_form_tflops": round(FLOPS_PER_PAIR_TERM * terms / (ps_ms * 1e-3) / 1e12, 3),
         "tile": dict({k: info[k] for k in ("rows_per_wave", "blocks_per_cu", "work_items", "groups", "mfma_shape")},
                      **({"mfma_outputs_per_wave": "%d x %d" % srm3.srm3_mfma_shape("fp32", info["mfma_shape"])}
@@ -597,7 +614,7 @@ def bench_serve(args, torch, srm3):
         "value": points / mk if mk else None, "unit": "grid points/s", "n_gpus": 1, "steps": 1, "warmup": 1,
         "ms_per_step": round(mk * 1e3, 1) if mk else None, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-        "config": {"pair_kernel": "matrix cores (FP32 MFMA)" if pk == "mfma" else "vector ALUs",
+        "config": {"pair_kernel": SPLIT_LABEL,
                    "workload": f"serving: {n} requests per rate, grids 64x256/256x1024/512x4096/1024x8192 "
                                f"lines (mix {mix}), U ~ U[20,45], Poisson arrivals (seed 42) at 0.3/0.6/0.9 x "
                                f"saturated throughput, continuous batching (32 slots, 48 GiB arena, "
@@ -804,7 +821,7 @@ def bench_bridge(args, torch, srm3):
     prof = srm3.srm3_profile_read(plan)
     srm3.srm3_profile_enable(plan, False)
     ps_ms = prof["pairsum"][0] / max(1, prof["pairsum"][1])
-    fpt = MFMA_FLOPS_PER_PAIR_TERM   # both pair-sum kernels execute 6 flops per term
+    bound, fpt, peak = pair_roofline(wl.n_kappa, mfma)
     tf = fpt * terms * B / (ps_ms * 1e-3) / 1e12
     log(f"[bench] bridge direct fp32: {dt * 1e3:.2f} ms/step (plan {plan_s:.2f} s)")
     kplan = srm3.srm3_plan(wl.grid_dict(), S, bis, "fp32")
@@ -888,11 +905,10 @@ def bench_bridge(args, torch, srm3):
         "config": {"workload": f"bridge example: {wl.n_kappa}x{wl.n_omega} lines, {wl.n_x}x{wl.n_t} field, "
                                f"wind bispectrum alpha {wl.alpha} through the partial-bicoherence recursion, "
                                f"cap {wl.cap}, {B} realizations"},
-        "roofline": {"bound": "mfma" if mfma else "alu",
-                     "kernel": mfma_kernel_name(wl, B) if mfma else "pairsum_kernel<float,8,true>",
-                     "achieved": round(tf, 3), "peak": PEAK_FP32_MFMA_TFLOPS if mfma else FMA_ISSUE_FP32_TFLOPS,
-                     "unit": "TFLOP/s",
-                     "frac": round(tf / (PEAK_FP32_MFMA_TFLOPS if mfma else FMA_ISSUE_FP32_TFLOPS), 4),
+        "roofline": {"bound": bound,
+                     "kernel": "pairsum_split_kernel" if split_form(wl.n_kappa) else
+                     mfma_kernel_name(wl, B) if mfma else "pairsum_kernel<float,8,true>",
+                     "achieved": round(tf, 3), "peak": peak, "unit": "TFLOP/s", "frac": round(tf / peak, 4),
                      "flops_per_pair_term": fpt,
                      "traffic": None, "pair_terms_per_launch": terms * B, "avg_launch_ms": round(ps_ms, 4)},
         "cpu_baseline": None,
@@ -969,7 +985,25 @@ def main():
     kname = "mfma" if mfma else "vector"
     full = B == wl.batch
     complex_tflops = FLOPS_PER_PAIR_TERM * terms * B / (ps_ms * 1e-3) / 1e12
-    if mfma:
+    split = split_form(wl.n_kappa, args.mfma_shape if mfma else 0)
+    if split:
+        # 12 FP16 multiply-adds per pair term at the dense FP16 matrix rate; the
+        # clock falls to about 2.0 GHz under this load
+        achieved_tflops = SPLIT_FLOPS_PER_PAIR_TERM * terms * B / (ps_ms * 1e-3) / 1e12
+        roofline = {
+            "bound": "mfma",
+            "kernel": "pairsum_split_kernel (v_mfma_f32_16x16x32_f16)",
+            "achieved": round(achieved_tflops, 3),
+            "peak": PEAK_FP16_MFMA_TFLOPS,
+            "unit": "TFLOP/s",
+            "frac": round(achieved_tflops / PEAK_FP16_MFMA_TFLOPS, 4),
+            "traffic": None,
+            "pair_terms_per_launch": terms * B,
+            "flops_per_pair_term": SPLIT_FLOPS_PER_PAIR_TERM,
+            "avg_launch_ms": round(ps_ms, 4),
+            "pair_terms_per_s": terms * B / (ps_ms * 1e-3),
+        }
+    elif mfma:
         achieved_tflops = MFMA_FLOPS_PER_PAIR_TERM * terms * B / (ps_ms * 1e-3) / 1e12
         roofline = {
             "bound": "mfma",
@@ -1014,7 +1048,7 @@ def main():
     extra = {"pair_sum_complex_form": {
         "tflops": round(complex_tflops, 3),
         "note": "the same launch counted at 14 flops per pair term (complex product, weight, accumulate); "
-                "not a roofline figure: the kernel executes 6 flops per term"}}
+                f"not a roofline figure: the kernel executes {roofline['flops_per_pair_term']} flops per term"}}
     tb = transform_bytes(wl, B)
     tr = {}
     for k in ("phases", "tfft", "xfft"):
@@ -1039,12 +1073,11 @@ def main():
         log(f"[bench] plain fp32: {dtp * 1e3:.2f} ms per {B} realizations ({psteps} timed)")
     plans = {"fp32": plan32}
     fields = {"fp32": out32}
-    # ---- the other FP32 pair-sum kernel (vector ALUs, or the matrix cores) ----
-    if not args.no_plain:
-        other = "vector" if mfma else "mfma"
+    # ---- the FP32 matrix instructions' form (tile of 32 x 16 outputs per wave) ----
+    if not args.no_plain and split:
         planv = srm3.plan_from_workload(wl, "fp32")
-        if other == "mfma":
-            srm3.srm3_plan_set_algorithm(planv, "mfma")
+        srm3.srm3_plan_set_algorithm(planv, "mfma")
+        srm3.srm3_plan_set_mfma_shape(planv, 1)
         outv = torch.empty((B, wl.n_x, wl.n_t), dtype=torch.float32, device="cuda")
         srm3.srm3_profile_enable(planv, True)
         dtv = timed_steps(torch, lambda: srm3.srm3_generate(planv, seeds, outv), 1, 1)
@@ -1052,21 +1085,14 @@ def main():
         srm3.srm3_profile_enable(planv, False)
         vms = pv["pairsum"][0] / max(1, pv["pairsum"][1])
         vtf = MFMA_FLOPS_PER_PAIR_TERM * terms * B / (vms * 1e-3) / 1e12
-        leg = {"grid_points_per_s": grid_points / dtv, "ms_per_step": round(dtv * 1e3, 3),
-               "pairsum_avg_launch_ms": round(vms, 4), "pair_terms_per_s": terms * B / (vms * 1e-3),
-               "issued_tflops": round(vtf, 3)}
-        if other == "vector":
-            leg.update({"kernel": f"pairsum_kernel<float,{srm3.srm3_rows_per_wave(planv)},true>", "bound": "alu",
-                        "frac_of_fma_issue_ceiling": round(vtf / FMA_ISSUE_FP32_TFLOPS, 4),
-                        "fma_issue_ceiling_tflops": FMA_ISSUE_FP32_TFLOPS,
-                        "valu_issue_frac": counter_valu(wl, "vector") if full else None})
-        else:
-            leg.update({"kernel": mfma_kernel_name(wl, B, mrows, mcols), "bound": "mfma",
-                        "frac_of_fp32_matrix_peak": round(vtf / PEAK_FP32_MFMA_TFLOPS, 4)})
-        extra[f"{other}_pairsum"] = leg
-        plans[f"fp32_{other}"] = planv
-        fields[f"fp32_{other}"] = outv
-        log(f"[bench] batched fp32, {other} pair sum: {dtv * 1e3:.2f} ms/step")
+        extra["mfma_fp32_pairsum"] = {
+            "grid_points_per_s": grid_points / dtv, "ms_per_step": round(dtv * 1e3, 3),
+            "pairsum_avg_launch_ms": round(vms, 4), "pair_terms_per_s": terms * B / (vms * 1e-3),
+            "issued_tflops": round(vtf, 3), "kernel": mfma_kernel_name(wl, B, *srm3.srm3_mfma_shape("fp32", 1)),
+            "bound": "mfma", "frac_of_fp32_matrix_peak": round(vtf / PEAK_FP32_MFMA_TFLOPS, 4)}
+        plans["fp32_mfma_fp32"] = planv
+        fields["fp32_mfma_fp32"] = outv
+        log(f"[bench] batched fp32, FP32 matrix instructions: {dtv * 1e3:.2f} ms/step")
     # ---- batched FP64 ----
     if not args.no_fp64 and wl.n_t <= 8192:
         plan64 = srm3.plan_from_workload(wl, "fp64")
@@ -1080,7 +1106,7 @@ def main():
         p64 = srm3.srm3_profile_read(plan64)
         ps64 = p64["pairsum"][0] / max(1, p64["pairsum"][1])
         extra["fp64_grid_points_per_s"] = grid_points / dt64
-        extra["fp64_pair_kernel"] = "matrix cores (FP64 MFMA)" if mfma else "vector ALUs"
+        extra["fp64_pair_kernel"] = "matrix cores (FP64 MFMA)"
         extra["fp64_pairsum_ms"] = round(ps64, 3)
         # 6 flops per pair term (three real products on the matrix cores, or three
         # FP64 FMAs on the vector ALUs) against the FP64 peak (matrix and vector
@@ -1177,7 +1203,7 @@ def main():
         "config": {"workload": f"{wl.name}: {wl.n_kappa}x{wl.n_omega} lines, {wl.n_x}x{wl.n_t} field, "
                                f"batch {B}, bicoherence support {wl.support_w}",
                    "global_batch": B, "precision": "fp32 fixed-point phases, compensated pair sums",
-                   "pair_kernel": "matrix cores (FP32 MFMA)" if mfma else "vector ALUs"},
+                   "pair_kernel": SPLIT_LABEL if split else "matrix cores (FP32 MFMA)" if mfma else "vector ALUs"},
         "roofline": roofline,
         "cpu_baseline": cpu,
         "kernel_avg_ms": kernel_ms,
