@@ -51,8 +51,9 @@ using gmut = T *;
 #endif
 
 // Buffer loads: a uniform resource, a per-lane byte offset and a uniform byte
-// offset, so stepping the uniform one costs no vector address arithmetic (and
-// reads past the buffer return zero).
+// offset, so stepping the uniform one costs no vector address arithmetic.  A
+// per-lane offset past the buffer loads zero; the uniform offset takes no part
+// in that check, so it stays within the buffer.
 #if defined(__HIP_DEVICE_COMPILE__)
 using brsrc = __amdgpu_buffer_rsrc_t;
 __device__ __forceinline__ brsrc make_brsrc(const void *p, unsigned bytes)

@@ -313,6 +313,10 @@ hipError_t launch_wsh(int precision, const void *wt, const Geometry &g, const Kf
 // Weighted frequency autoconvolution Y of the kappa-DFT rows Z.  The sheared
 // weight table has at least kYpairChunk + 2 zero rows after its 2 W - 1.
 constexpr int kYpairChunk = 32;
+// The DFT row that row r of a wave's tile reads, of the `rows` it has: past the
+// last one that row again (its sums are not stored).  A row is a scalar offset
+// of a buffer load, which the bounds check of the buffer does not cover.
+__host__ __device__ inline int ypair_row(int r, int rows) { return r < rows ? r : rows - 1; }
 hipError_t launch_ypair(int precision, const Geometry &g, const KfftGeom &k, const void *Z, void *Y, const void *wh,
                         int batch, hipStream_t st);
 // tw: e^{+2 pi i n / M}, n < M

@@ -75,7 +75,8 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
     const int iw_lo = max(-W + 1, (kw_lo + 1) >> 1);
     const int iw_hi = min(W - 1, a.one_sided ? kw_hi : kw_hi + W - 1);
     const int nchunk = __builtin_amdgcn_readfirstlane(iw_hi >= iw_lo ? (iw_hi - iw_lo + C) / C : 0);
-    // rows past the last read zero, lanes past a row's ends read past the buffer
+    // rows past the last read that one, lanes past a row's ends get a vector
+    // offset past the buffer (and load zero)
     const unsigned row_bytes = static_cast<unsigned>(ncw) * E;
     const brsrc zr = make_brsrc(Zq, static_cast<unsigned>(rows) * row_bytes);
     const unsigned wrow_bytes = static_cast<unsigned>(a.nca) * E;
@@ -96,8 +97,9 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
         T2 z0[R], z1[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            z0[r] = bload(zr, v0, static_cast<unsigned>(r) * row_bytes, T(0));
-            z1[r] = bload(zr, v1, static_cast<unsigned>(r) * row_bytes, T(0));
+            const unsigned ro = static_cast<unsigned>(ypair_row(r, rows)) * row_bytes;
+            z0[r] = bload(zr, v0, ro, T(0));
+            z1[r] = bload(zr, v1, ro, T(0));
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
         const int ic0 = iwc + W - 1;
         if constexpr (ALDS) {
             static_assert(64 % R == 0 && C * R % 64 == 0, "staging shape");
-            const int r = lane % R;
+            const int r = ypair_row(lane % R, rows);
 #pragma unroll
             for (int i = 0; i < C * R / 64; ++i) {
                 const int ic = ic0 + lane / R + 64 / R * i;
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
                 const cptr<T> p = as_const(reinterpret_cast<const T *>(Zq)) + 2 * min(ic0 + s + u, ncw - 1);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const long o = 2 * static_cast<long>(min(r, rows - 1)) * ncw;
+                    const long o = 2 * static_cast<long>(ypair_row(r, rows)) * ncw;
                     av[u][r].x = p[o];
                     av[u][r].y = p[o + 1];
                 }
