@@ -1209,7 +1209,7 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
         const Workspace ws = carve_workspace(gr.g, b->precision, static_cast<int>(gr.members.size()),
                                              static_cast<char *>(b->ws.p) + gr.ws_off);
         const size_t lines = static_cast<size_t>(gr.g.nk) * gr.g.nc;
-        const size_t a_bytes = gr.form == DirectForm::split ? split_operand_bytes(gr.g)
+        const size_t a_bytes = gr.form == DirectForm::split ? split_operand_bytes(gr.g.nk, gr.g.ncw)
                                                             : a_slots(b->precision) * gr.g.ncw * gr.g.nkp * e;
         const bool mfma = gr.form == DirectForm::mfma;
         const int mr = mfma_rows_per_group(b->precision, b->mfma_shape);

@@ -169,6 +169,23 @@ hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, cons
 // the subnormals for all but the smallest components).
 constexpr double kSplitMaxFactor = 32.0, kSplitMinFactor = 1.0 / 64;
 constexpr int kSplitMinRows = 32;   // (the FP16 parts fit the a operand region from 30 rows on)
+// Its operand of one realization: [2W - 1 columns][re hi, re lo, im hi, im lo]
+// [8 + nk8] FP16, kappa-contiguous: eight zeros (rows -8 .. -1), then nk8 =
+// n_kappa rounded up to 8 rows (zero past n_kappa); after the last column 16
+// bytes that the starts of its last rows read and no stored row uses.
+__host__ __device__ inline int split_nk8(int nk) { return (nk + 7) & ~7; }
+__host__ __device__ inline int split_seg(int nk) { return split_nk8(nk) + 8; }
+// Byte offset within a column of the eight values of part p from row k on;
+// where all of them are past the rows (or before the zeros, or there is no such
+// part), that of the column's eight zeros.
+__host__ __device__ inline unsigned split_start(int nk, int p, int k)
+{
+    return p < 4 && k >= -8 && k < split_nk8(nk) ? static_cast<unsigned>(p * split_seg(nk) + 8 + k) * 2u : 0u;
+}
+__host__ __device__ inline size_t split_operand_bytes(int nk, int ncw)
+{
+    return static_cast<size_t>(8) * ncw * split_seg(nk) + 16;
+}
 bool split_supported(const Geometry &g, int precision);
 hipError_t launch_phases_split(const Geometry &g, const uint64_t *seeds, const uint64_t *seeds_dev, int batch,
                                const Workspace &ws, const double *lr, hipStream_t st);
@@ -184,7 +201,6 @@ struct SplitItems {
 hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const SplitItems &n, int tiles,
                                       unsigned *counters, hipStream_t st);
 int split_shape(const Geometry &g);   // 0: 256 x 32 lines, 1: 128 x 64, 2: 64 x 128
-size_t split_operand_bytes(const Geometry &g);   // a operand of one realization
 inline size_t split_counter_words(int tiles) { return kSplitShapes + static_cast<size_t>(tiles); }
 // A work list under construction: whole tiles of requests, in the order added.
 struct SplitTile {

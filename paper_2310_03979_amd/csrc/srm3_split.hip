@@ -34,12 +34,6 @@ typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 constexpr float kSplitScale = 1024.0f;            // z is held times 2^10
 constexpr float kSplitUnscale = 1.0f / 1024.0f;   // applied to W and to the sums
 
-// FP16 operand layout of one realization: [2W - 1 columns][re hi, re lo, im
-// hi, im lo][8 + nk8], kappa-contiguous: eight zeros (rows -8 .. -1), then
-// nk8 = n_kappa rounded up to 8 rows (zero past n_kappa).
-__host__ __device__ inline int split_nk8(int nk) { return (nk + 7) & ~7; }
-__host__ __device__ inline int split_seg(int nk) { return split_nk8(nk) + 8; }
-
 // ---------------------------------------------------------------------------
 // Phases with the split operand: the tiles of phase_kernel (64 frequencies x
 // 64 rows), the same words and phase rows; the four FP16 parts are staged in
@@ -101,7 +95,7 @@ __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const
     if (!planes) return;
     __syncthreads();
     const int nk8 = split_nk8(g.nk), seg = split_seg(g.nk);
-    _Float16 *zb = zh + static_cast<long>(b) * 4 * g.ncw * seg;
+    _Float16 *zb = zh + static_cast<size_t>(b) * (split_operand_bytes(g.nk, g.ncw) / 2);
     if (k0 == 0) {
         const int ic = ic0 + static_cast<int>(threadIdx.x >> 2);
         if (ic >= 0 && ic < g.ncw)
@@ -177,7 +171,7 @@ template <int NV> struct SplitShape {
 };
 
 struct SplitArgs {
-    const void *zh;      // [B][ncw][4][8 + nk8] FP16
+    const void *zh;      // [B] operands (split_operand_bytes)
     const void *wtab;    // [ncw][ncw] float2
     void *tout;          // [B][nk][nc] float2
     Geometry g;
@@ -257,7 +251,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
     const int lane = tid & 63, li = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int v = wave % NV, cw = wave / NV;
-    const int nk8 = split_nk8(g.nk), seg = split_seg(g.nk);
+    const int seg = split_seg(g.nk);
     const int Wm1 = g.W - 1;
     int lo, hi;
     split_range(g.nw, g.nc, g.W, S::CB, cg, lo, hi);
@@ -275,7 +269,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
     const int kw0 = col0 - (g.nw - 1);                   // frequency of the lane's first column
     const unsigned col_bytes = static_cast<unsigned>(seg) * 8u;   // of a column's four parts
     const unsigned ncw = 2u * Wm1 + 1u;
-    const brsrc zr = make_brsrc(zh, ncw * col_bytes), wr = make_brsrc(wtab, ncw * ncw * 8u);
+    const brsrc zr = make_brsrc(zh, ncw * col_bytes + 16u), wr = make_brsrc(wtab, ncw * ncw * 8u);
 
     float tre[2][2][4], tim[2][2][4];
 #pragma unroll
@@ -303,7 +297,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
 #pragma unroll
         for (int i = 0; i < ET; ++i) {
             const int t = tid + 512 * i, p = t / S::NS, k = eslot(t - p * S::NS) + D - S::JB;
-            e_off[i] = (p < 4 && k >= -8 && k <= nk8) ? static_cast<unsigned>(p * seg + 8 + k) * 2u : 0u;
+            e_off[i] = split_start(g.nk, p, k);
         }
         auto load_e = [&](int iw, uint4v (&x)[ET]) {
 #pragma unroll
@@ -317,7 +311,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
             }
         };
         // 16 bytes of column jw: the thread's part and rows of the pass
-        const unsigned b_off = S::JB * J + 8 * bg < nk8 ? static_cast<unsigned>(bp * seg + 8 + S::JB * J + 8 * bg) * 2u : 0u;
+        const unsigned b_off = split_start(g.nk, bp, S::JB * J + 8 * bg);
         auto load_b = [&](int jw) {
             const bool ok = jw > -g.W && jw < g.W;
             return load16(zr, ok ? b_off : 0u, ok ? static_cast<unsigned>(jw + Wm1) * col_bytes : 0u);
@@ -353,10 +347,8 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
         for (int t = tid; t < S::CB * 4 * BG; t += 512) {
             const int gq = t & (BG - 1), p = (t / BG) & 3, n = t / (4 * BG);
             const int jw = k0 - iw0 + n, j = S::JB * J + 8 * gq;
-            const bool ok = jw > -g.W && jw < g.W && j < nk8;
-            const uint4v x =
-                load16(zr, ok ? static_cast<unsigned>(jw + Wm1) * col_bytes + static_cast<unsigned>(p * seg + 8 + j) * 2u : 0u,
-                       0u);
+            const bool ok = jw > -g.W && jw < g.W;
+            const uint4v x = load16(zr, ok ? static_cast<unsigned>(jw + Wm1) * col_bytes + split_start(g.nk, p, j) : 0u, 0u);
             *reinterpret_cast<uint4v *>(ring + n * S::COL + p * S::PART + gq * 16) = reversed(x, p);
         }
         // weights of the products held, and of the next column
@@ -573,7 +565,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int t = tile / batch, b = tile - t * batch;
             rs = a.n_rs - 1 - t / a.n_cg;
             cg = t - (t / a.n_cg) * a.n_cg;
-            zh = static_cast<const char *>(a.zh) + static_cast<long>(b) * 8 * (2 * g.W - 1) * split_seg(g.nk);
+            zh = static_cast<const char *>(a.zh) + static_cast<size_t>(b) * split_operand_bytes(g.nk, 2 * g.W - 1);
             wtab = static_cast<const char *>(a.wtab);
             tout = static_cast<float2v *>(a.tout) + static_cast<long>(b) * g.nk * g.nc;
         }
@@ -674,7 +666,6 @@ hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const
 }
 
 int split_shape(const Geometry &g) { return split_nv(g.nk) == 8 ? 0 : (split_nv(g.nk) == 4 ? 1 : 2); }
-size_t split_operand_bytes(const Geometry &g) { return static_cast<size_t>(8) * g.ncw * split_seg(g.nk); }
 
 std::vector<SplitTile> split_tiles(const Geometry &g, int req)
 {

@@ -29,9 +29,38 @@ static void ypair()
         }
 }
 
+// Operand of the split-FP16 pair sum: the 16 bytes that a block stages of any
+// start lie in it, in every column; those it may use are the rows they stand
+// for; and the operand fits the region the workspace keeps for it (three FP32
+// values per support column and row, rows padded to the rows per wave).
+static void split()
+{
+    for (int nk = 32; nk <= 700; ++nk) {
+        const int rs = nk <= 64 ? 64 : (nk <= 128 ? 128 : 256);
+        const unsigned col_bytes = static_cast<unsigned>(split_seg(nk)) * 8u;
+        for (int ncw : {1, 3, 2047})
+            for (int R : {2, 4, 8, 16}) {
+                const size_t nkp = static_cast<size_t>((nk + R - 1) / R * R);
+                CHECK(split_operand_bytes(nk, ncw) <= 12 * ncw * nkp, "split nk %d ncw %d R %d: operand", nk, ncw, R);
+            }
+        for (int p = 0; p < 8; ++p)
+            for (int k = -2 * rs - 8; k <= nk + 2 * rs; ++k) {
+                const unsigned o = split_start(nk, p, k);
+                for (int ncw : {1, 9})
+                    CHECK((ncw - 1) * static_cast<size_t>(col_bytes) + o + 16 <= split_operand_bytes(nk, ncw),
+                          "split nk %d part %d row %d: offset %u in the last of %d columns", nk, p, k, o, ncw);
+                if (p < 4 && k > -8 && k < nk)
+                    CHECK(o == static_cast<unsigned>(p * split_seg(nk) + 8 + k) * 2u, "split nk %d part %d row %d", nk, p, k);
+                else if (p < 4 && k >= split_nk8(nk))
+                    CHECK(o == 0, "split nk %d part %d row %d is past the rows", nk, p, k);
+            }
+    }
+}
+
 int main()
 {
     ypair();
+    split();
     if (!fails) std::printf("address bounds: ok\n");
     return fails != 0;
 }
