@@ -157,6 +157,9 @@ struct Slabs {
 };
 constexpr size_t kSlabBytes = size_t(16) << 20;
 size_t mfma_slab_bytes(const Geometry &g, int batch);   // of the default tile shape
+// Realizations of one launch of the FP64 form with `items` work items for one:
+// all of them stay below 2^30 (they are counted in 32 bits, a few past the end).
+inline int mfma_queue_batch(long items) { return static_cast<int>(items >= (1L << 30) ? 1 : (1L << 30) / items); }
 constexpr int kMfmaBlocksPerCu = 3;   // the matrix-core kernels run 3 waves per SIMD
 // Kernels of the direct form: vector ALUs, matrix cores, split FP16.
 enum class DirectForm { vector, mfma, split };

@@ -2269,20 +2269,28 @@ static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch,
         q.next = static_cast<unsigned *>(ws.g);
         q.done = q.next + 1;
         q.n_ct = n_ct;
-        q.tiles = batch * a.n_rg * n_ct;
         int chunks = 1;
         for (int c0 = 0; c0 < g.nc; c0 += 16 * CT) chunks = std::max(chunks, mfma_tile_chunks(g, c0, 16 * CT));
-        q.n_items = q.tiles * chunks;
-        const long n = static_cast<long>(batch) * g.nk * g.nc;
+        const long lines = static_cast<long>(g.nk) * g.nc, n = lines * batch;
         // one call's chunks apart where they fit beside the workspace: no chain
         // of ordered additions (32x64 lines: 0.17 -> 0.09 ms)
         q.slabs = chunks > 1 && slabs.p && static_cast<size_t>(chunks) * n * sizeof(double2) <= slabs.n
                       ? static_cast<double2 *>(slabs.p) : nullptr;
-        const hipError_t e = launch_fill_u32(q.next, 1 + static_cast<size_t>(q.tiles), 0u, st);
-        if (e != hipSuccess) return e;
-        const int blocks = std::min((q.n_items + kWavesPerBlock - 1) / kWavesPerBlock, 3 * 256);
-        pairsum_mfma_queue_kernel<RT, CT><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a, q);
-        if (q.slabs)
+        // realizations of one launch: its items are counted in 32 bits
+        const int per = mfma_queue_batch(static_cast<long>(a.n_rg) * n_ct * chunks);
+        for (int b0 = 0; b0 < batch; b0 += per) {
+            a.batch = std::min(per, batch - b0);
+            a.zrow = static_cast<const double2 *>(ws.zrow) + b0 * lines;
+            a.zcol = static_cast<const double *>(ws.zcol) + b0 * ALayout<double>::NS * static_cast<long>(g.ncw) * g.nkp;
+            a.tout = static_cast<double2 *>(ws.tsum) + b0 * lines;
+            q.tiles = a.batch * a.n_rg * n_ct;
+            q.n_items = q.tiles * chunks;
+            const hipError_t e = launch_fill_u32(q.next, 1 + static_cast<size_t>(q.tiles), 0u, st);
+            if (e != hipSuccess) return e;
+            const int blocks = std::min((q.n_items + kWavesPerBlock - 1) / kWavesPerBlock, 3 * 256);
+            pairsum_mfma_queue_kernel<RT, CT><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a, q);
+        }
+        if (q.slabs)   // (one launch: they hold the whole call)
             sum_slabs_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), 256, 0, st>>>(
                 q.slabs, g, batch, 16 * CT, static_cast<double2 *>(ws.tsum));
         return hipGetLastError();
