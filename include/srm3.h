@@ -251,10 +251,11 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *   SRM3_ALGO_DIRECT     enumerates the unordered pairs of every line (the
  *                        coefficient sum of Section 4.1 / 4.3 as written), on
  *                        the vector ALUs, or in FP64 with n_kappa >= 16 on the
- *                        matrix cores, or in FP32 with n_kappa >= 32 and partner
+ *                        matrix cores, or in FP32 with n_kappa >= 32, partner
  *                        factors (line_r, wind, product) of magnitude 0 or
- *                        1/64 .. 32 in split FP16 on the matrix cores (see
- *                        SRM3_ALGO_MFMA).
+ *                        1/64 .. 32 and pair weights whose largest magnitude
+ *                        is 0 or 2^-64 .. 2^64 in split FP16 on the matrix
+ *                        cores (see SRM3_ALGO_MFMA).
  *   SRM3_ALGO_KAPPA_FFT  the same sum, reorganised: the weights depend on the
  *                        frequency indices only, so the kappa part of the
  *                        ordered pair sum is a linear convolution of phase
@@ -278,7 +279,7 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *                        with 16x16x4 MFMAs (FP32: v_mfma_f32_16x16x4_f32 with
  *                        two-sum flushes; FP64: v_mfma_f64_16x16x4_f64).  FP32
  *                        plans with the default tile shape, n_kappa >= 32 and
- *                        partner factors of moderate range (as above) take
+ *                        factors and weights of moderate range (as above) take
  *                        each FP32 product as three FP16 products of split
  *                        phases with FP32 sums, as accurate as the FP32 form
  *                        (v_mfma_f32_16x16x32_f16).  Same

@@ -590,6 +590,15 @@ srm3_status srm3_plan(const srm3_grid *grid, const srm3_spectrum *spectrum, cons
         const double r = std::hypot(lrx[2 * l], lrx[2 * l + 1]);
         if (r > kSplitMaxFactor || (r > 0.0 && r < kSplitMinFactor)) p->split_range = false;
     }
+    // (sqrt(g2_i g2_j) is largest at the largest g2)
+    double wmax = 0.0;
+    if (!hcx.empty())
+        for (size_t i = 0; i < hcx.size() / 2; ++i) wmax = std::max(wmax, std::hypot(hcx[2 * i], hcx[2 * i + 1]));
+    else if (bs.kind == SRM3_BISPEC_SEPARABLE)
+        wmax = *std::max_element(bs.g2, bs.g2 + ncw);
+    else if (bs.kind == SRM3_BISPEC_DENSE)
+        wmax = std::sqrt(*std::max_element(bs.b2, bs.b2 + static_cast<size_t>(ncw) * ncw));
+    if (wmax > kSplitMaxWeight || (wmax > 0.0 && wmax < kSplitMinWeight)) p->split_range = false;
     if (!lrx.empty() && (s = upload_bytes(p->lr, lrx.data(), lrx.size() * sizeof(double), st))) return s;
     if (!hcx.empty() && (s = upload(p->wtab, hcx, precision, st))) return s;   // the prescribed H as the weights
     if ((s = upload(p->tw_t, pass_twiddles(nt), precision, st))) return s;

@@ -171,6 +171,10 @@ hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, cons
 // or between the bounds (2^10 z must stay below 65504, and the low part above
 // the subnormals for all but the smallest components).
 constexpr double kSplitMaxFactor = 32.0, kSplitMinFactor = 1.0 / 64;
+// and for pair weights whose largest magnitude lies between these: the form
+// holds W 2^-10 and T 2^10, which must neither overflow nor lose bits below
+// FP32's normal numbers.
+constexpr double kSplitMaxWeight = 1.8446744073709552e19, kSplitMinWeight = 5.421010862427522e-20;   // 2^64, 2^-64
 constexpr int kSplitMinRows = 32;   // (the FP16 parts fit the a operand region from 30 rows on)
 // Its operand of one realization: [2W - 1 columns][re hi, re lo, im hi, im lo]
 // [8 + nk8] FP16, kappa-contiguous: eight zeros (rows -8 .. -1), then nk8 =
@@ -395,7 +399,7 @@ struct srm3_plan_s {
     srm3::DevBuf lc, lr;     // per-line complex bicoherence factors c, rho (interleaved FP64), or empty
     int ws_batch = 0;
     srm3::DevBuf slabs;   // partial sums of small FP64 calls (see Slabs), with the workspace
-    bool split_range = true;   // the phase factors' magnitudes suit the split-FP16 pair sum
+    bool split_range = true;   // the phase factors' and weights' magnitudes suit the split-FP16 pair sum
     bool gaussian = false;   // zero bicoherence: no pair sum (2nd-order SRM)
     bool process = false;    // the 1-D process: one kappa line, one-sided spectrum and pairs
     bool hashed = false;     // bispectrum generated per pair in the kernel (SRM3_BISPEC_HASHED)
