@@ -12,9 +12,10 @@
 //     2^10 z = hi + lo + e,  |e| <= 2^-24 2^10 for |z| <= 1,
 // so that three FP16 products (hi hi + hi lo + lo hi) with FP32 accumulation
 // replace one FP32 product: 12 FP16 multiply-adds per pair term at 16 times
-// the FP32 matrix rate.  What a product drops (lo lo and e) is below 2^-23 of
-// the largest factor; the sums are shorter than those of the FP32 form.  The
-// weight is applied in FP32, once per output and partner column.
+// the FP32 matrix rate.  A product drops lo lo and the two e: below 1.5 x 2^-23
+// of the largest factors' product.  The weight is applied in FP32, once per
+// output and partner column, and the weighted products are summed in FP32 on
+// three levels: groups of columns, items, tiles.
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const
 // the swizzled starts (bit 3 flipped by bit 4) put every group on distinct
 // banks.
 //
-// Work item: one tile x kSplitChunk partner columns.  Items are taken from a
+// Work item: one tile x split_chunk partner columns.  Items are taken from a
 // queue in order (chunk by chunk over all tiles) and each adds its sums to the
 // tile's in `tout` after the item of the previous chunk has, so the sum does
 // not depend on which blocks run the items or on how many requests share the
@@ -154,7 +155,16 @@ __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const
 // over the partner columns, spills); both operands of the next step in a
 // second register set (spills, 100 ms); 32x32x16 MFMAs (7 % slower).
 // ---------------------------------------------------------------------------
-constexpr int kSplitChunk = 64;   // (one item: about 0.15 ms at 256 rows)
+// Partner columns of an item, by the support alone: 64 (0.15 ms at 256 rows;
+// 128 leave single calls short of items, 64x128 lines 0.156 -> 0.254 ms), more
+// where a tile would have over 64 items, each of which rounds its sum once.
+__host__ __device__ inline int split_chunk(int W) { return 64 * ((2 * W - 1 + 4095) / 4096); }
+// FP32 sums of this many columns are added to the item's: a column rounds a sum
+// of eight, not of the whole item.  Relative error of the coefficients (root
+// mean square, against 64 bits) with one sum per item, so, and in the FP32
+// MFMAs' form: 32x512 lines 2.2e-7, 1.5e-7, 2.1e-7; 64x2048 2.8e-7, 1.7e-7,
+// 2.1e-7; 256x1024 2.4e-7, 1.5e-7, 4.0e-7.  Groups of 4 the same; the time too.
+constexpr int kSplitGroup = 8;
 
 template <int NV> struct SplitShape {
     static constexpr int RS = 32 * NV;              // rows of a tile
@@ -198,7 +208,7 @@ __host__ __device__ inline int split_chunks(const Geometry &g, int cb, int cg)
 {
     int lo, hi;
     split_range(g.nw, g.nc, g.W, cb, cg, lo, hi);
-    return hi < lo ? 1 : (hi - lo) / kSplitChunk + 1;
+    return hi < lo ? 1 : (hi - lo) / split_chunk(g.W) + 1;
 }
 
 // (the 16-byte loads of a's starts are aligned to two bytes only)
@@ -255,8 +265,9 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
     const int Wm1 = g.W - 1;
     int lo, hi;
     split_range(g.nw, g.nc, g.W, S::CB, cg, lo, hi);
-    const int iw0 = lo + chunk * kSplitChunk;
-    const int iw1 = min(iw0 + kSplitChunk, hi + 1);
+    const int ch = split_chunk(g.W);
+    const int iw0 = lo + chunk * ch;
+    const int iw1 = min(iw0 + ch, hi + 1);
     if (chunk > 0 && iw0 > hi) return;   // this tile has fewer chunks
 
     const int k0 = cg * S::CB - (g.nw - 1);   // frequency of the tile's first column
@@ -271,13 +282,14 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
     const unsigned ncw = 2u * Wm1 + 1u;
     const brsrc zr = make_brsrc(zh, ncw * col_bytes + 16u), wr = make_brsrc(wtab, ncw * ncw * 8u);
 
-    float tre[2][2][4], tim[2][2][4];
+    // sums of the item, and of its last (up to kSplitGroup) columns
+    float tre[2][2][4], tim[2][2][4], gre[2][2][4], gim[2][2][4];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tre[m][c][e] = tim[m][c][e] = 0.0f;
+            for (int e = 0; e < 4; ++e) tre[m][c][e] = tim[m][c][e] = gre[m][c][e] = gim[m][c][e] = 0.0f;
 
     // staging of the a column: thread t takes the starts t, t + 512, .. of the four parts
     constexpr int ET = (4 * S::NS + 511) / 512;
@@ -375,7 +387,7 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
         for (int iw = iw0; iw < iw1; ++iw) {
             const int buf = (iw - iw0) & 1;
             float4v pre[2][2], pia[2][2], pib[2][2];   // re = pre, im = pia - pib (the ring holds -im of b)
-        // T += W P of the column before
+        // G += W P
         auto update = [&]() {
 #pragma unroll
             for (int m = 0; m < 2; ++m)
@@ -384,10 +396,10 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float pr = pre[m][c][e], pi = pia[m][c][e] - pib[m][c][e];
-                        tre[m][c][e] = __builtin_fmaf(w[c].x, pr, tre[m][c][e]);
-                        tre[m][c][e] = __builtin_fmaf(-w[c].y, pi, tre[m][c][e]);
-                        tim[m][c][e] = __builtin_fmaf(w[c].x, pi, tim[m][c][e]);
-                        tim[m][c][e] = __builtin_fmaf(w[c].y, pr, tim[m][c][e]);
+                        gre[m][c][e] = __builtin_fmaf(w[c].x, pr, gre[m][c][e]);
+                        gre[m][c][e] = __builtin_fmaf(-w[c].y, pi, gre[m][c][e]);
+                        gim[m][c][e] = __builtin_fmaf(w[c].x, pi, gim[m][c][e]);
+                        gim[m][c][e] = __builtin_fmaf(w[c].y, pr, gim[m][c][e]);
                     }
         };
             const bool more = iw + 1 < iw1;
@@ -477,6 +489,18 @@ __device__ __forceinline__ void split_item(unsigned char *smem, const SplitGeom 
                 w[1] = wn[1];
                 if (more) load_w(iw + 1, wn);
                 update();
+                if (((iw - iw0) & (kSplitGroup - 1)) == kSplitGroup - 1 || !more) {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int c = 0; c < 2; ++c)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                tre[m][c][e] += gre[m][c][e];
+                                tim[m][c][e] += gim[m][c][e];
+                                gre[m][c][e] = gim[m][c][e] = 0.0f;
+                            }
+                }
             }
             if (more) {
                 store_e(buf ^ 1, ex);
