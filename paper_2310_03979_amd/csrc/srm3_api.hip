@@ -246,7 +246,7 @@ srm3_status check_batch(srm3_plan_t p, const void *seeds, int32_t batch, const v
 }
 
 srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, const Workspace &ws,
-                           const KfftWorkspace &kw, hipStream_t st)
+                           const KfftWorkspace &kw, const Slabs &slabs, hipStream_t st)
 {
     srm3_status s;
     if ((s = event_pair(p, 0, st, true))) return s;
@@ -274,7 +274,7 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
         e = launch_pairsum_split(p->g, p->wtab.p, batch, ws, st);
         if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
     } else if (form == DirectForm::mfma) {
-        e = launch_pairsum_mfma(p->g, p->precision, shape, p->wtab.p, batch, ws, Slabs{p->slabs.p, p->slabs.n}, st);
+        e = launch_pairsum_mfma(p->g, p->precision, shape, p->wtab.p, batch, ws, slabs, st);
         if (e != hipSuccess) return dev_err(e, "matrix-core pair-sum kernel");
     } else {
         e = launch_pairsum(p->g, p->precision, p->wtab.p, batch, ws, st);
@@ -284,12 +284,12 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     return SRM3_OK;
 }
 
-// phases and pair sums with the plan's own kappa-FFT workspace
+// phases and pair sums with the plan's own kappa-FFT workspace and chunk sums
 srm3_status run_front(srm3_plan_t p, const uint64_t *seeds, int32_t batch, const Workspace &ws, hipStream_t st)
 {
     KfftWorkspace kw;
     if (kfft_family(p->algo)) kw = carve_kfft(p->g, p->kg, p->precision, batch, p->kws.p);
-    return run_front_kfft(p, seeds, batch, ws, kw, st);
+    return run_front_kfft(p, seeds, batch, ws, kw, Slabs{p->slabs.p, p->slabs.n}, st);
 }
 
 srm3_status run_back(srm3_plan_t p, int mode, const void *cin, int32_t batch, const Workspace &ws, void *out,
@@ -1008,16 +1008,18 @@ srm3_status srm3_generate_noalloc(srm3_plan_t plan, const uint64_t *seeds, int32
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     ProfPause pause(plan);
     const Workspace ws = carve_workspace(plan->g, plan->precision, batch, base);
-    if (kfft_family(plan->algo)) {
-        // the kappa-DFT stage takes its workspace from the scratch too
-        const KfftWorkspace kw = carve_kfft(plan->g, plan->kg, plan->precision, batch,
-                                            static_cast<char *>(base) + main_bytes);
-        if ((s = run_front_kfft(plan, seeds, batch, ws, kw, st))) return s;
-    } else if (plan->gaussian && !plan->lr.p) {
+    if (plan->gaussian && !plan->lr.p && !kfft_family(plan->algo))
         return run_back(plan, 2, nullptr, batch, ws, out_dev, st, seeds);
-    } else if ((s = run_front(plan, seeds, batch, ws, st))) {
-        return s;
-    }
+    // the kappa-DFT stage and the chunk sums of the FP64 pair sum (where they
+    // fit) take their workspace from the scratch too
+    char *rest = static_cast<char *>(base) + main_bytes;
+    KfftWorkspace kw;
+    Slabs slabs;
+    if (kfft_family(plan->algo))
+        kw = carve_kfft(plan->g, plan->kg, plan->precision, batch, rest);
+    else if (kScratchBytes > main_bytes)
+        slabs = Slabs{rest, std::min(kScratchBytes - main_bytes, kSlabBytes)};
+    if ((s = run_front_kfft(plan, seeds, batch, ws, kw, slabs, st))) return s;
     return run_back(plan, 0, nullptr, batch, ws, out_dev, st);
 }
 
