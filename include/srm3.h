@@ -228,10 +228,14 @@ srm3_status srm3_coefficients(srm3_plan_t plan, const uint64_t *seeds, int32_t b
 srm3_status srm3_transform(srm3_plan_t plan, const void *C_dev, int32_t batch,
                            void *out_dev, void *hip_stream);
 
-/* Device workspace bytes that srm3_generate needs for `batch` realizations. */
+/* Device workspace bytes that srm3_generate needs for `batch` realizations.
+ * FP64 plans on the matrix cores keep up to 16 MiB beside it, the partial sums
+ * of as many realizations as fit (none where one realization's do not): calls
+ * without them, as where their allocation failed, give the same result. */
 srm3_status srm3_workspace_bytes(srm3_plan_t plan, int32_t batch, size_t *bytes);
 
-/* Fill the plan's whole device workspace for `batch` realizations (grown as
+/* Fill the plan's whole device workspace for `batch` realizations and its
+ * partial sums (grown as
  * srm3_generate would grow it, so that call may allocate) with the 32-bit
  * pattern `word`, by a kernel on hip_stream.  For tests and tooling: with a
  * NaN pattern, a later generation shows that no kernel lets a value it did not

@@ -205,6 +205,20 @@ srm3_status event_pair(srm3_plan_t p, int kernel, hipStream_t st, bool begin)
 // The pair-sum algorithms that go through a DFT along kappa (own workspace and tables).
 bool kfft_family(int algo) { return algo == SRM3_ALGO_KAPPA_FFT || algo == SRM3_ALGO_FFT2D; }
 
+// Tile shape of a plan's direct form (that of SRM3_ALGO_DIRECT is the default one).
+int direct_shape(srm3_plan_t p) { return p->algo == SRM3_ALGO_MFMA ? p->mfma_shape : 0; }
+
+// Chunk sums that calls of up to `batch` realizations keep beside the workspace:
+// those of as many realizations as fit kSlabBytes, for plans whose pair sum is
+// the FP64 matrix-core form.
+size_t slab_bytes(srm3_plan_t p, int batch)
+{
+    if (p->precision != SRM3_FP64 || p->gaussian || p->hashed || kfft_family(p->algo) ||
+        direct_form(p, direct_shape(p)) != DirectForm::mfma)
+        return 0;
+    const size_t one = mfma_slab_bytes(p->g, 1);
+    return one <= kSlabBytes ? one * std::min<size_t>(batch, kSlabBytes / one) : 0;
+}
 
 srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
 {
@@ -216,9 +230,13 @@ srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
             return fail(SRM3_E_NOMEM, "workspace hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
         }
         p->ws_batch = batch;
-        // small FP64 grids (without it the sums take a little longer)
-        if (p->precision == SRM3_FP64 && !p->gaussian && !p->hashed && !p->slabs.p &&
-            mfma_slab_bytes(p->g, 1) <= kSlabBytes && p->slabs.alloc(kSlabBytes) != hipSuccess)
+    }
+    if (const size_t want = slab_bytes(p, batch); want > p->slabs.n) {
+        // (without them the sums take longer; a capture that came without a
+        // call before it stays free of allocations)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+            p->slabs.alloc(want) != hipSuccess)
             (void)hipGetLastError();
     }
     if (kfft_family(p->algo) && batch > p->kws_batch) {
@@ -252,8 +270,7 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
     if ((s = event_pair(p, 0, st, true))) return s;
     Workspace wp = ws;
     if (p->gaussian || p->hashed || kfft_family(p->algo)) wp.zcol = nullptr;   // no a operand planes needed
-    // (the tile shape of SRM3_ALGO_DIRECT is the default one)
-    const int shape = p->algo == SRM3_ALGO_MFMA ? p->mfma_shape : 0;
+    const int shape = direct_shape(p);
     const bool direct = !p->gaussian && !p->hashed && !kfft_family(p->algo);
     const DirectForm form = direct ? direct_form(p, shape) : DirectForm::vector;
     const bool split = form == DirectForm::split;
@@ -824,6 +841,7 @@ srm3_status srm3_workspace_fill(srm3_plan_t plan, int32_t batch, uint32_t word, 
     srm3_status s = ensure_workspace(plan, batch, st);
     if (s) return s;
     hipError_t e = launch_fill_u32(plan->ws.p, plan->ws.n / 4, word, st);
+    if (e == hipSuccess && plan->slabs.p) e = launch_fill_u32(plan->slabs.p, plan->slabs.n / 4, word, st);
     if (e == hipSuccess && kfft_family(plan->algo)) e = launch_fill_u32(plan->kws.p, plan->kws.n / 4, word, st);
     if (e != hipSuccess) return dev_err(e, "fill kernel");
     return SRM3_OK;
