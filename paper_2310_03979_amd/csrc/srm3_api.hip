@@ -216,8 +216,8 @@ size_t slab_bytes(srm3_plan_t p, int batch)
     if (p->precision != SRM3_FP64 || p->gaussian || p->hashed || kfft_family(p->algo) ||
         direct_form(p, direct_shape(p)) != DirectForm::mfma)
         return 0;
-    const size_t one = mfma_slab_bytes(p->g, 1);
-    return one <= kSlabBytes ? one * std::min<size_t>(batch, kSlabBytes / one) : 0;
+    const size_t one = f64_slab_bytes(p->g, direct_shape(p), 1);
+    return one > 0 && one <= kSlabBytes ? one * std::min<size_t>(batch, kSlabBytes / one) : 0;
 }
 
 srm3_status ensure_workspace(srm3_plan_t p, int batch, hipStream_t st)
@@ -291,7 +291,8 @@ srm3_status run_front_kfft(srm3_plan_t p, const uint64_t *seeds, int32_t batch, 
         e = launch_pairsum_split(p->g, p->wtab.p, batch, ws, st);
         if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
     } else if (form == DirectForm::mfma) {
-        e = launch_pairsum_mfma(p->g, p->precision, shape, p->wtab.p, batch, ws, slabs, st);
+        e = p->precision == SRM3_FP64 ? launch_pairsum_f64(p->g, shape, p->wtab.p, batch, ws, slabs, st)
+                                      : launch_pairsum_mfma(p->g, shape, p->wtab.p, batch, ws, st);
         if (e != hipSuccess) return dev_err(e, "matrix-core pair-sum kernel");
     } else {
         e = launch_pairsum(p->g, p->precision, p->wtab.p, batch, ws, st);
@@ -1127,7 +1128,7 @@ struct srm3_batch_s {
     int blocks_per_cu = 2;
     int n_cu = 256;
     DevBuf ws, seeds, scales, sptr, outs, preq;
-    // work lists of the persistent launches: vector items, matrix-core items
+    // work lists of the persistent launches: vector items, FP32 matrix-core items
     struct Queue {
         DevBuf items, begin, next;
         int n = 0;
@@ -1135,8 +1136,10 @@ struct srm3_batch_s {
     Queue queue[2];
     int n_items = 0;                   // all work items
     DevBuf split_items, split_ctr;     // work list of the split-FP16 pair sum and its counters
-    SplitItems split_n;
+    WorkItems split_n;
     int split_tiles = 0;
+    DevBuf f64_items, f64_ctr;         // the same of the FP64 matrix-core pair sum
+    int f64_n = 0, f64_tiles = 0;
     uint64_t *seeds_host = nullptr;    // pinned staging
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
@@ -1228,7 +1231,7 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
         double cost;
     };
     const size_t e = b->precision == SRM3_FP64 ? 8 : 4;
-    SplitList split;
+    WorkList split, f64;
     srm3_status s;
     std::vector<std::vector<It>> per_req[2];   // vector, matrix-core items
     std::vector<double> req_cost(b->n, 0.0);
@@ -1251,7 +1254,11 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
                                 static_cast<char *>(ws.zcol) + slot * a_bytes,
                                 static_cast<char *>(ws.tsum) + slot * lines * 2 * e, gr.plan->wtab.p);
             if (gr.form == DirectForm::split) {
-                split.add(d, gr.g);
+                split.add(split_shape(gr.g), split_tiles(gr.g, d));
+                continue;
+            }
+            if (mfma && b->precision == SRM3_FP64) {
+                f64.add(0, f64_tiles(gr.g, b->mfma_shape, d));
                 continue;
             }
             for (int kb = nrb - 1; kb >= 0; --kb)
@@ -1309,6 +1316,16 @@ srm3_status batch_layout(srm3_batch_t b, int R, hipStream_t st)
         const hipError_t er = b->split_ctr.alloc(split_counter_words(b->split_tiles) * sizeof(unsigned));
         if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
     }
+    WorkItems f64_n;
+    const std::vector<unsigned char> fitems = f64.items(&f64_n);
+    b->f64_tiles = f64.tiles();
+    b->f64_n = f64_n.begin[1];
+    b->n_items += b->f64_n;
+    if (b->f64_tiles > 0) {
+        if ((s = upload_bytes(b->f64_items, fitems.data(), fitems.size(), st))) return s;
+        const hipError_t er = b->f64_ctr.alloc(f64_counter_words(b->f64_tiles) * sizeof(unsigned));
+        if (er != hipSuccess) return fail(SRM3_E_NOMEM, "hipMalloc: %s", hipGetErrorString(er));
+    }
     return upload_bytes(b->preq, reqs.data(), reqs.size(), st);
 }
 
@@ -1342,6 +1359,11 @@ srm3_status batch_launch(srm3_batch_t b, hipStream_t st, bool time_pairsum)
         e = launch_pairsum_split_items(b->preq.p, b->split_items.p, b->split_n, b->split_tiles,
                                        static_cast<unsigned *>(b->split_ctr.p), st);
         if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
+    }
+    if (b->f64_tiles > 0) {
+        e = launch_pairsum_f64_items(b->mfma_shape, b->preq.p, b->f64_items.p, b->f64_n, b->f64_tiles,
+                                     static_cast<unsigned *>(b->f64_ctr.p), st);
+        if (e != hipSuccess) return dev_err(e, "matrix-core pair-sum kernel");
     }
     for (int kind = 0; kind < 2; ++kind) {
         const auto &qu = b->queue[kind];

@@ -149,22 +149,30 @@ struct MfmaShape {
 };
 constexpr int kMfmaShapes = 3;
 MfmaShape mfma_shape(int precision, int shape);
-// `slabs`: device memory for the FP64 form's partial sums of small calls (may be
-// empty; the sums are the same).
+// Realizations of one launch of the FP64 form with `items` work items for one:
+// all of them stay below 2^30 (they are counted in 32 bits, a few past the end).
+inline int mfma_queue_batch(long items) { return static_cast<int>(items >= (1L << 30) ? 1 : (1L << 30) / items); }
+constexpr int kMfmaBlocksPerCu = 3;   // the FP32 matrix-core kernels run 3 waves per SIMD
+// Kernels of the direct form: vector ALUs, matrix cores, split FP16.
+enum class DirectForm { vector, mfma, split };
+// FP32:
+hipError_t launch_pairsum_mfma(const Geometry &g, int shape, const void *wtab, int batch, const Workspace &ws,
+                               hipStream_t st);
+// FP64 (srm3_f64.hip); `slabs`: device memory for the partial sums of small
+// calls (may be empty; the sums are the same).
 struct Slabs {
     void *p = nullptr;
     size_t n = 0;
 };
 constexpr size_t kSlabBytes = size_t(16) << 20;
-size_t mfma_slab_bytes(const Geometry &g, int batch);   // of the default tile shape
-// Realizations of one launch of the FP64 form with `items` work items for one:
-// all of them stay below 2^30 (they are counted in 32 bits, a few past the end).
-inline int mfma_queue_batch(long items) { return static_cast<int>(items >= (1L << 30) ? 1 : (1L << 30) / items); }
-constexpr int kMfmaBlocksPerCu = 3;   // the matrix-core kernels run 3 waves per SIMD
-// Kernels of the direct form: vector ALUs, matrix cores, split FP16.
-enum class DirectForm { vector, mfma, split };
-hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, const void *wtab, int batch,
-                               const Workspace &ws, const Slabs &slabs, hipStream_t st);
+size_t f64_slab_bytes(const Geometry &g, int shape, int batch);
+hipError_t launch_pairsum_f64(const Geometry &g, int shape, const void *wtab, int batch, const Workspace &ws,
+                              const Slabs &slabs, hipStream_t st);
+// The same over a work list (its items of one shape, see WorkList); `counters`
+// holds f64_counter_words(tiles) words (zeroed here).
+hipError_t launch_pairsum_f64_items(int shape, const void *reqs, const void *items, int n_items, int tiles,
+                                    unsigned *counters, hipStream_t st);
+inline size_t f64_counter_words(int tiles) { return 1 + static_cast<size_t>(tiles); }
 // The FP32 direct form on the FP16 matrix cores with split phases (see
 // srm3_split.hip): its phase kernel (the a operand region of the workspace
 // then holds the FP16 parts) and pair sum, for phase factors of magnitude zero
@@ -202,31 +210,35 @@ hipError_t launch_pairsum_split(const Geometry &g, const void *wtab, int batch, 
 // begin[i + 1]), the chunks of a tile in ascending order; `counters` holds
 // kSplitShapes + tiles words (zeroed here).
 constexpr int kSplitShapes = 3;
-struct SplitItems {
+struct WorkItems {
     int begin[kSplitShapes + 1] = {0, 0, 0, 0};
 };
-hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const SplitItems &n, int tiles,
+hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const WorkItems &n, int tiles,
                                       unsigned *counters, hipStream_t st);
 int split_shape(const Geometry &g);   // 0: 256 x 32 lines, 1: 128 x 64, 2: 64 x 128
 inline size_t split_counter_words(int tiles) { return kSplitShapes + static_cast<size_t>(tiles); }
-// A work list under construction: whole tiles of requests, in the order added.
-struct SplitTile {
-    int req, rs, cg, chunks;
+// A work list under construction: tiles of requests (row and column tile, items,
+// pair terms), in the order added.
+struct WorkTile {
+    int req, rs, cg;
+    int chunks;   // 0: one item for the whole tile (FP64)
     double cost;
+    int items() const { return chunks > 0 ? chunks : 1; }
 };
+constexpr int kTileWhole = -1;   // chunk of such an item
 // Tiles of one request, heaviest first (cost: pair terms).
-std::vector<SplitTile> split_tiles(const Geometry &g, int req);
-class SplitList {
+std::vector<WorkTile> split_tiles(const Geometry &g, int req);
+std::vector<WorkTile> f64_tiles(const Geometry &g, int shape, int req);
+class WorkList {
 public:
-    void add(int req, const Geometry &g);                       // every tile of a request
-    void add(int shape, const std::vector<SplitTile> &tiles);   // some tiles of one request
+    void add(int shape, const std::vector<WorkTile> &tiles);   // tiles of one request
     int tiles() const { return n_tiles_; }
     // Items by shape, requests by descending cost, each chunk by chunk.
-    std::vector<unsigned char> items(SplitItems *n);
+    std::vector<unsigned char> items(WorkItems *n);
 
 private:
     struct Run {
-        std::vector<SplitTile> tiles;
+        std::vector<WorkTile> tiles;
         double cost;
     };
     std::vector<Run> runs_[kSplitShapes];
@@ -253,6 +265,7 @@ int waves_per_block();
 // 32-bit fill of device memory by a kernel (graph-safe, unlike hipMemsetAsync)
 hipError_t launch_fill_u32(void *p, size_t words, uint32_t v, hipStream_t st);
 constexpr int kXcds = 8;
+constexpr int kCus = 256;
 // mode 0: assemble C from pair sums and phases; mode 1: read C from `cin`;
 // mode 2 (zero bicoherence): C = A_pure e^{i phi} with the phases drawn here
 // from the host `seeds` (no phase rows are read).

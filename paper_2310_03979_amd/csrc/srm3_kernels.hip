@@ -6,19 +6,17 @@
 //                (k_kappa, k_omega mod n_t), inverse DFT along t (Stockham, LDS)
 //  xfft        : inverse DFT along x over the n_kappa live rows, real part out
 #include <algorithm>
-#include <climits>
 #include <cstring>
 #include <string>
 
 #include "srm3_device.hpp"
 #include "srm3_internal.hpp"
+#include "srm3_mfma.hpp"
 
 namespace srm3 {
 
 namespace {
 
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <typename T>
 __device__ __forceinline__ void two_sum(T &s, T &c, T x)
@@ -51,22 +49,6 @@ __device__ __forceinline__ gptr<T> as_global(const T *p)
     return (gptr<T>)p;
 }
 
-
-// Layout of the a operand (re, re + im, im - re) of support column ic, row kk:
-// FP32 keeps three kappa-contiguous planes (a block's rows load as wide scalar
-// loads); FP64 interleaves the three values per row, padded to four, so that
-// rows load one at a time and the scalar register window stays small.
-template <typename T> struct ALayout;
-template <> struct ALayout<float> {
-    static constexpr int ES = 1;       // element stride between rows
-    static constexpr int NS = 3;       // slots per (column, row)
-    __device__ static long plane(const Geometry &g) { return static_cast<long>(g.ncw) * g.nkp; }
-};
-template <> struct ALayout<double> {
-    static constexpr int ES = 4;
-    static constexpr int NS = 4;
-    __device__ static long plane(const Geometry &) { return 1; }
-};
 
 // ---------------------------------------------------------------------------
 // Phases with the a operand.  A block covers a tile of 64 frequencies (16
@@ -523,7 +505,7 @@ __global__ __launch_bounds__(256) void pairsum_kernel(PairsumArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Pair sum on the matrix cores (FP32).
+// Pair sum on the matrix cores, FP32 (products and loads: srm3_mfma.hpp).
 //
 // Grouped by the kappa split jk instead of the partner column, the sum of the
 // vector kernel reads
@@ -539,8 +521,8 @@ __global__ __launch_bounds__(256) void pairsum_kernel(PairsumArgs a)
 // (re + im, im, re):
 //     P1 += A_re (B_re + B_im),  P2 += (A_re + A_im) B_im,  P3 += (A_im - A_re) B_re,
 //     Re T = P1 - P2,  Im T = P1 + P3.
-// FP32 sums are flushed into error-free (two-sum) accumulators every few
-// hundred steps; FP64 sums stay whole.  A wave owns RT x CT tiles of 16 x 16
+// The sums are flushed into error-free (two-sum) accumulators every few hundred
+// steps.  (FP64: the same products, see srm3_f64.hip.)  A wave owns RT x CT tiles of 16 x 16
 // outputs; partner columns are stepped 4 at a time (outer loop, weights kept
 // in registers), kappa splits one at a time (inner loop).  Operand layouts of
 // the 16x16x4 MFMAs (lane l, i = l % 16, q = l / 16): A[i][q], B[q][i] in;
@@ -561,270 +543,57 @@ struct MfmaArgs {
     int flush_steps;    // kappa steps between two-sum flushes
 };
 
-// Partner columns of a chunk of the FP64 form, by the grid alone (the sums do
-// not depend on the batch).  A wave's item of 32 columns takes 80-160 us at 128
-// rows, long beside the 10 us of an ordered addition; the smallest grids take
-// 8 (11 us at 32x64, 64 waves for one realization), their chunks summed apart.
-__host__ __device__ inline int mfma_chunk(const Geometry &g) { return g.nk * g.nc <= 16384 ? 8 : 32; }
-
 constexpr int kMfmaFlushSteps = 256;   // 1024 products per accumulator element
 constexpr long kMfmaPrioBlocks = 16 * 256;   // launches of at least 16 blocks per CU raise the MFMA priority
 
-// Per-precision pieces of the matrix-core pair sum: the 16x16x4 MFMA and its
-// output row layout, the a
-// operand layout (FP32: three kappa-contiguous planes; FP64: the three values
-// of a (column, row) side by side, rows 32 bytes apart) and whether the sums
-// are flushed into two-sum pairs (FP32 only).
-template <typename T> struct MfmaT;
-template <> struct MfmaT<float> {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    static constexpr bool COMP = true;
-    static constexpr bool PLANAR = true;
-    static constexpr unsigned ROW_BYTES = 4;
-    __device__ static v4 mfma(float x, float y, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); }
-    __device__ static int drow(int q, int e) { return 4 * q + e; }   // output row of lane group q, element e
-    __device__ static float aload(brsrc r, unsigned voff, unsigned soff) { return bload32(r, voff, soff); }
-};
-template <> struct MfmaT<double> {
-    typedef double v4 __attribute__((ext_vector_type(4)));
-    static constexpr bool COMP = false;
-    static constexpr bool PLANAR = false;
-    static constexpr unsigned ROW_BYTES = 32;
-    __device__ static v4 mfma(double x, double y, v4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0); }
-    __device__ static int drow(int q, int e) { return q + 4 * e; }   // rows interleaved (checked on the device)
-    __device__ static double aload(brsrc r, unsigned voff, unsigned soff) { return bload64(r, voff, soff); }
-};
-
-// One wave's RT x CT tiles of one realization: output rows from K0 = 16 RT rg,
-// columns c0 .. c0 + 16 CT - 1.  PRIO: issue each split's MFMAs at raised
-// wave priority.
-//
-// FP64 sums the partner columns in chunks of mfma_chunk(nk) and adds the
-// chunks in order, chunks chunk0 .. chunk1 - 1 here (the tile's last one at
-// most).  Chunk first_chunk starts the sum in tout_b.  With `done` the chunks
-// of a tile may be run by several waves: each waits until those before it are
-// added.
-template <typename T, int RT, int CT, bool PRIO>
-__device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<T>::v2 *__restrict__ zrow_b,
-                                          const T *__restrict__ zcol_b, const typename vec<T>::v2 *__restrict__ wtab,
-                                          typename vec<T>::v2 *__restrict__ tout_b, int rg, int c0, int flush_steps,
-                                          int chunk0, int chunk1, int first_chunk, unsigned *done)
+// One wave's RT x CT tiles of one realization in FP32: output rows from
+// 16 RT rg, columns c0 .. c0 + 16 CT - 1, sums flushed into two-sum pairs.
+template <int RT, int CT, bool PRIO>
+__device__ __forceinline__ void mfma_tile(const Geometry &g, const float2 *__restrict__ zrow_b,
+                                          const float *__restrict__ zcol_b, const float2 *__restrict__ wtab,
+                                          float2 *__restrict__ tout_b, int rg, int c0, int flush_steps)
 {
-    using T2 = typename vec<T>::v2;
-    using M = MfmaT<T>;
-    using V4 = typename M::v4;
+    using M = MfmaT<float>;
+    using V4 = M::v4;
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lq = lane >> 4;
     const int K0 = rg * 16 * RT;
     const int Wm1 = g.W - 1;
     const int kw_lo = c0 - (g.nw - 1);
     const int kw_hi = min(c0 + 16 * CT - 1, g.nc - 1) - (g.nw - 1);
-    const int iw_lo = max(-Wm1, kw_lo - Wm1);
-    const int iw_hi = min(Wm1, kw_hi + Wm1);
-    const int ch = M::COMP ? INT_MAX / 2 : mfma_chunk(g);
-    if (!M::COMP) {
-        chunk1 = min(chunk1, iw_hi < iw_lo ? 1 : (iw_hi - iw_lo) / ch + 1);
-        if (chunk0 >= chunk1) return;
-    }
-    const int kk_max = min(K0 + 16 * RT - 1, g.nk - 1);
-    const int jk_end = kk_max / 2;   // last kappa split any row of the wave uses
-    const int jb = K0 / 2;           // splits below jb are at full weight for every row
-
-    const long lines = static_cast<long>(g.nk) * g.nc;
-    const long plane = static_cast<long>(g.ncw) * g.nkp;
-    // b rows through a buffer resource (uniform row offset, per-lane column).
-    // The a planes' resource starts `shift` rows before them: per-lane offsets
-    // stay fixed for a partner step and the split moves the uniform offset
-    // (shift - jk rows, never negative).  Reads of rows a split does not use
-    // stay inside the plan's workspace (the phase rows precede the a planes);
-    // their values (not necessarily finite) are replaced by zero, skipped with
-    // their tile, or land in an output row that is not stored.
-    const unsigned row_bytes = static_cast<unsigned>(g.nc * sizeof(T2));
-    const brsrc zb = make_brsrc(zrow_b, static_cast<unsigned>(lines * sizeof(T2)));
-    const int shift = jk_end + 2;
-    constexpr unsigned RS = M::ROW_BYTES;   // bytes between kappa rows of one a value
-    const brsrc za = make_brsrc(reinterpret_cast<const char *>(zcol_b) - static_cast<long>(shift) * RS,
-                                static_cast<unsigned>(ALayout<T>::NS * plane * sizeof(T) + (shift + 64) * RS));
-    // bytes between the three a values of one (column, row)
-    const unsigned plane_bytes = M::PLANAR ? static_cast<unsigned>(plane * sizeof(T)) : static_cast<unsigned>(sizeof(T));
-
-    // FP32 flushes the MFMA sums into two-sum pairs; FP64 keeps them whole
-    constexpr int NS = M::COMP ? 4 : 1;
     V4 P1[RT][CT], P2[RT][CT], P3[RT][CT];
-    T sre[RT][CT][NS], cre[RT][CT][NS], sim[RT][CT][NS], cim[RT][CT][NS];
+    float sre[RT][CT][4], cre[RT][CT][4], sim[RT][CT][4], cim[RT][CT][4];
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            P1[r][c] = P2[r][c] = P3[r][c] = V4{T(0), T(0), T(0), T(0)};
+            P1[r][c] = P2[r][c] = P3[r][c] = V4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int e = 0; e < NS; ++e) sre[r][c][e] = cre[r][c][e] = sim[r][c][e] = cim[r][c][e] = T(0);
+            for (int e = 0; e < 4; ++e) sre[r][c][e] = cre[r][c][e] = sim[r][c][e] = cim[r][c][e] = 0.0f;
         }
     auto flush = [&]() {
-        if constexpr (M::COMP) {
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-#pragma unroll
-                    for (int e = 0; e < NS; ++e) {
-                        two_sum(sre[r][c][e], cre[r][c][e], P1[r][c][e] - P2[r][c][e]);
-                        two_sum(sim[r][c][e], cim[r][c][e], P1[r][c][e] + P3[r][c][e]);
-                    }
-                    P1[r][c] = P2[r][c] = P3[r][c] = V4{T(0), T(0), T(0), T(0)};
-                }
-        }
-    };
-
-    // Partner step iw0 (4 columns): the lane's a-plane byte offset (row
-    // K0 + li of column ic, plane 0), its b column offsets and weights.
-    auto setup = [&](int s0, unsigned &ao, unsigned (&bo)[CT], T2 (&w)[CT]) {
-        const int iw = s0 + lq;
-        const int ic = min(iw + Wm1, g.ncw - 1);
-        ao = static_cast<unsigned>(ic * g.nkp + K0 + li) * RS;
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const int col = c0 + 16 * c + li;
-            const int jw = col - (g.nw - 1) - iw;
-            const bool ok = col < g.nc && iw <= Wm1 && jw > -g.W && jw < g.W;
-            w[c].x = T(0);
-            w[c].y = T(0);
-            if (ok) w[c] = wtab[static_cast<long>(iw + Wm1) * g.ncw + (jw + Wm1)];
-            bo[c] = ok ? static_cast<unsigned>(jw + g.nw - 1) * static_cast<unsigned>(sizeof(T2)) : 0u;
-        }
-    };
-    // operands of split jk: b phases per column tile, a planes per row tile
-    auto load_split = [&](T2 (&zs)[CT], T (&as)[RT][3], unsigned ao, const unsigned (&bo)[CT], int jk) {
-#pragma unroll
-        for (int c = 0; c < CT; ++c) zs[c] = bload(zb, bo[c], static_cast<unsigned>(jk) * row_bytes, T(0));
-        const unsigned so = static_cast<unsigned>(shift - jk) * RS;
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const unsigned o = ao + 16u * RS * r;
-            as[r][0] = M::aload(za, o, so);
-            as[r][1] = M::aload(za, o + plane_bytes, so);
-            as[r][2] = M::aload(za, o + 2 * plane_bytes, so);
-        }
-    };
-    auto split = [&](int jk, bool tail, const unsigned (&bo)[CT], const T2 (&wc)[CT], const T2 (&zc)[CT],
-                     const T (&ac)[RT][3]) {
-        T bs[CT], bi[CT], br[CT];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const T Br = fma_(wc[c].x, zc[c].x, -wc[c].y * zc[c].y);
-            const T Bi = fma_(wc[c].x, zc[c].y, wc[c].y * zc[c].x);
-            bs[c] = Br + Bi;
-            bi[c] = Bi;
-            br[c] = Br;
-        }
-        // PRIO: the split's MFMAs at raised wave priority, so that a wave that
-        // reaches them issues them back to back while the other waves of the
-        // SIMD do their VALU work
-        if (PRIO) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            if (tail && 2 * jk > K0 + 16 * r + 15) continue;   // no row of this tile uses the split
-            T x0 = ac[r][0], x1 = ac[r][1], x2 = ac[r][2];
-            if (tail) {
-                // rows above the split keep their values, the split's own row
-                // is halved, rows below it are replaced by zero (a select, not
-                // a product: the values read there lie outside the a planes
-                // and need not be finite)
-                const int kk = K0 + 16 * r + li;
-                const T h = 2 * jk == kk ? T(0.5) : T(1);
-                const bool use = 2 * jk <= kk;
-                x0 = use ? x0 * h : T(0);
-                x1 = use ? x1 * h : T(0);
-                x2 = use ? x2 * h : T(0);
-            }
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                P1[r][c] = M::mfma(x0, bs[c], P1[r][c]);
-                P2[r][c] = M::mfma(x1, bi[c], P2[r][c]);
-                P3[r][c] = M::mfma(x2, br[c], P3[r][c]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    two_sum(sre[r][c][e], cre[r][c][e], P1[r][c][e] - P2[r][c][e]);
+                    two_sum(sim[r][c][e], cim[r][c][e], P1[r][c][e] + P3[r][c][e]);
+                }
+                P1[r][c] = P2[r][c] = P3[r][c] = V4{0.0f, 0.0f, 0.0f, 0.0f};
             }
-        }
-        if (PRIO) __builtin_amdgcn_s_setprio(0);
     };
-
-    // FP64 sums chunk by chunk, each added to the tile's in order
-    for (int chunk = M::COMP ? 0 : chunk0;;) {
-    const int i0 = M::COMP ? iw_lo : iw_lo + chunk * ch;
-    const int i1 = M::COMP ? iw_hi : min(iw_hi, i0 + ch - 1);
     int since = 0;
-    for (int iw0 = i0; iw0 <= i1; iw0 += 4) {
-        unsigned ao;
-        unsigned boff[CT];
-        T2 wc[CT];
-        setup(iw0, ao, boff, wc);
-        // two operand sets: even splits in set 0, odd ones in set 1; each
-        // split first requests the next split's operands (the scheduling
-        // barrier keeps those loads ahead of this split's MFMAs; past the
-        // last split they read unused rows)
-        T2 z0[CT], z1[CT];
-        T a0[RT][3], a1[RT][3];
-        load_split(z0, a0, ao, boff, 0);
-        auto pair = [&](int jk, bool tail, bool both) {
-            load_split(z1, a1, ao, boff, jk + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            split(jk, tail, boff, wc, z0, a0);
-            if (!both) return;
-            load_split(z0, a0, ao, boff, jk + 2);
-            __builtin_amdgcn_sched_barrier(0);
-            split(jk + 1, tail, boff, wc, z1, a1);
-        };
-        // jb = K0 / 2 is even: the bulk ends on a set-0 split
-        int jk = 0;
-        for (; jk < jb; jk += 2) pair(jk, false, true);      // every row of the wave at full weight
-        for (; jk + 1 <= jk_end; jk += 2) pair(jk, true, true);
-        if (jk <= jk_end) pair(jk, true, false);
-        since += jk_end + 1;
-        if (M::COMP && since >= flush_steps) {
-            flush();
-            since = 0;
-        }
-    }
+    mfma_columns<float, RT, CT, PRIO>(g, zrow_b, zcol_b, wtab, rg, c0, max(-Wm1, kw_lo - Wm1), min(Wm1, kw_hi + Wm1), P1, P2,
+                                      P3, [&](int splits) {
+                                          since += splits;
+                                          if (since >= flush_steps) {
+                                              flush();
+                                              since = 0;
+                                          }
+                                      });
     flush();
-    // FP64: onto the sums of the chunks before
-    const bool add = !M::COMP && chunk > first_chunk;
-    if (add && done) wait_count(done, static_cast<unsigned>(chunk));
-    T2 v[RT][CT][4];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if constexpr (M::COMP) {
-                    v[r][c][e].x = sre[r][c][e] + cre[r][c][e];
-                    v[r][c][e].y = sim[r][c][e] + cim[r][c][e];
-                } else {
-                    v[r][c][e].x = P1[r][c][e] - P2[r][c][e];
-                    v[r][c][e].y = P1[r][c][e] + P3[r][c][e];
-                }
-            }
-    if (add) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            T2 old[CT][4];
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const T2 *p = tout_b + static_cast<long>(min(K0 + 16 * r + M::drow(lq, e), g.nk - 1)) * g.nc +
-                                  min(c0 + 16 * c + li, g.nc - 1);
-                    old[c][e].x = coherent_load(&p->x);
-                    old[c][e].y = coherent_load(&p->y);
-                }
-#pragma unroll
-            for (int c = 0; c < CT; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[r][c][e].x += old[c][e].x;
-                    v[r][c][e].y += old[c][e].y;
-                }
-        }
-    }
 #pragma unroll
     for (int r = 0; r < RT; ++r)
 #pragma unroll
@@ -833,105 +602,16 @@ __device__ __forceinline__ void mfma_tile(const Geometry &g, const typename vec<
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int kk = K0 + 16 * r + M::drow(lq, e);
-                if (kk < g.nk && col < g.nc) {
-                    T2 *p = tout_b + static_cast<long>(kk) * g.nc + col;
-                    if (M::COMP) {
-                        *p = v[r][c][e];
-                    } else {
-                        coherent_store(&p->x, v[r][c][e].x);
-                        coherent_store(&p->y, v[r][c][e].y);
-                    }
-                }
+                if (kk < g.nk && col < g.nc)
+                    tout_b[static_cast<long>(kk) * g.nc + col] =
+                        make_float2(sre[r][c][e] + cre[r][c][e], sim[r][c][e] + cim[r][c][e]);
             }
         }
-    if constexpr (M::COMP) break;
-    ++chunk;
-    if (done) {
-        wait_stores();
-        if (lane == 0) set_count(done, static_cast<unsigned>(chunk));
-    }
-    if (chunk >= chunk1) break;
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) P1[r][c] = P2[r][c] = P3[r][c] = V4{T(0), T(0), T(0), T(0)};
-    }
 }
 
-// The FP64 form over a queue of (tile, chunk) items, one wave each, taken in
-// order (chunk by chunk over all tiles) by four waves at a time: a wave waits
-// only for items taken before its own by running waves, or beside it.
-struct MfmaQueue {
-    unsigned *next;   // zero at launch
-    unsigned *done;   // chunks added per wave tile, zero at launch
-    int n_ct;         // column tiles
-    int tiles;        // batch * n_rg * n_ct
-    int n_items;      // tiles * chunks of the widest tile
-    double2 *slabs;   // or null: [chunks][batch][nk][nc], each chunk's sums apart (added by sum_slabs_kernel)
-};
-
-// Chunks of the column tile that starts at column c0.
-__host__ __device__ inline int mfma_tile_chunks(const Geometry &g, int c0, int cols)
-{
-    const int lo = c0 - (g.nw - 1), hi = (c0 + cols - 1 < g.nc - 1 ? c0 + cols - 1 : g.nc - 1) - (g.nw - 1);
-    const int i0 = lo - (g.W - 1) > -(g.W - 1) ? lo - (g.W - 1) : -(g.W - 1);
-    const int i1 = hi + g.W - 1 < g.W - 1 ? hi + g.W - 1 : g.W - 1;
-    return i1 < i0 ? 1 : (i1 - i0) / mfma_chunk(g) + 1;
-}
-
-// The chunks' sums, added in the order of the queue form.
-__global__ __launch_bounds__(256) void sum_slabs_kernel(const double2 *__restrict__ slabs, Geometry g, int batch,
-                                                        int cols, double2 *__restrict__ tout)
-{
-    const long n = static_cast<long>(batch) * g.nk * g.nc;
-    const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int col = static_cast<int>(i % g.nc);
-    const int chunks = mfma_tile_chunks(g, col / cols * cols, cols);
-    double2 t = slabs[i];
-    for (int c = 1; c < chunks; ++c) {
-        const double2 x = slabs[c * n + i];
-        t.x += x.x;
-        t.y += x.y;
-    }
-    tout[i] = t;
-}
-
-template <int RT, int CT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void pairsum_mfma_queue_kernel(MfmaArgs a,
-                                                                                                        MfmaQueue q)
-{
-    const Geometry &g = a.g;
-    const long lines = static_cast<long>(g.nk) * g.nc;
-    const long plane = static_cast<long>(g.ncw) * g.nkp;
-    __shared__ int s_base[2];
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    for (int turn = 0;; turn ^= 1) {
-        // (one atomic per block: 3072 waves on one counter would wait 0.1 ms for their turns)
-        if (threadIdx.x == 0) s_base[turn] = static_cast<int>(atomicAdd(q.next, static_cast<unsigned>(kWavesPerBlock)));
-        __syncthreads();
-        const int base = __builtin_amdgcn_readfirstlane(s_base[turn]);
-        if (base >= q.n_items) return;
-        const int item = base + wave;
-        if (item >= q.n_items) continue;
-        const int chunk = item / q.tiles, tile = item - chunk * q.tiles;
-        // heaviest row groups first, realizations innermost
-        const int k = tile / a.batch, b = tile - k * a.batch;
-        const int rg = a.n_rg - 1 - k / q.n_ct, ct = k - (k / q.n_ct) * q.n_ct;
-        mfma_tile<double, RT, CT, true>(g, static_cast<const double2 *>(a.zrow) + b * lines,
-                                         static_cast<const double *>(a.zcol) + b * ALayout<double>::NS * plane,
-                                         static_cast<const double2 *>(a.wtab),
-                                         q.slabs ? q.slabs + (static_cast<long>(chunk) * a.batch + b) * lines
-                                                 : static_cast<double2 *>(a.tout) + b * lines,
-                                         rg, 16 * CT * ct, a.flush_steps, chunk, chunk + 1, q.slabs ? chunk : 0,
-                                         q.slabs ? nullptr : q.done + tile);
-    }
-}
-
-template <typename T, int RT, int CT, bool PRIO>
+template <int RT, int CT, bool PRIO>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void pairsum_mfma_kernel(MfmaArgs a)
 {
-    using T2 = typename vec<T>::v2;
     const Geometry &g = a.g;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int bid = blockIdx.x;
@@ -955,9 +635,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
     if (c0 >= g.nc) return;
     const long lines = static_cast<long>(g.nk) * g.nc;
     const long plane = static_cast<long>(g.ncw) * g.nkp;
-    mfma_tile<T, RT, CT, PRIO>(g, static_cast<const T2 *>(a.zrow) + b * lines,
-                         static_cast<const T *>(a.zcol) + b * ALayout<T>::NS * plane, static_cast<const T2 *>(a.wtab),
-                         static_cast<T2 *>(a.tout) + b * lines, rg, c0, a.flush_steps, 0, 1, 0, nullptr);
+    mfma_tile<RT, CT, PRIO>(g, static_cast<const float2 *>(a.zrow) + b * lines,
+                            static_cast<const float *>(a.zcol) + b * ALayout<float>::NS * plane,
+                            static_cast<const float2 *>(a.wtab), static_cast<float2 *>(a.tout) + b * lines, rg, c0,
+                            a.flush_steps);
 }
 
 // Persistent pair sum over an uneven work list.  Work items (request, row
@@ -1013,10 +694,9 @@ __global__ __launch_bounds__(256) void pairsum_persistent(PersistArgs a)
 
 // The same queues with matrix-core items: (request, row group of 16 RT rows,
 // column group of kWavesPerBlock x 16 CT columns).
-template <typename T, int RT, int CT>
+template <int RT, int CT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void pairsum_persistent_mfma(PersistArgs a)
 {
-    using T2 = typename vec<T>::v2;
     __shared__ int s_item;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int home = blockIdx.x % kNumXcd;
@@ -1043,9 +723,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
         const PReq rq = a.reqs[w.req];
         const int c0 = (w.cg * kWavesPerBlock + wave) * 16 * CT;
         if (c0 < rq.g.nc)
-            mfma_tile<T, RT, CT, false>(rq.g, static_cast<const T2 *>(rq.zrow), static_cast<const T *>(rq.zcol),
-                                 static_cast<const T2 *>(rq.wtab), static_cast<T2 *>(rq.tsum), w.kb, c0,
-                                 kMfmaFlushSteps, 0, INT_MAX, 0, nullptr);
+            mfma_tile<RT, CT, false>(rq.g, static_cast<const float2 *>(rq.zrow), static_cast<const float *>(rq.zcol),
+                                     static_cast<const float2 *>(rq.wtab), static_cast<float2 *>(rq.tsum), w.kb, c0,
+                                     kMfmaFlushSteps);
     }
 }
 
@@ -2248,9 +1928,8 @@ hipError_t launch_pairsum(const Geometry &g, int precision, const void *wtab, in
     }
 }
 
-template <typename T, int RT, int CT>
-static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch, const Workspace &ws,
-                                 const Slabs &slabs, hipStream_t st)
+template <int RT, int CT>
+static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch, const Workspace &ws, hipStream_t st)
 {
     MfmaArgs a;
     a.zrow = ws.zrow;
@@ -2263,38 +1942,6 @@ static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch,
     const int n_ct = (g.nc + 16 * CT - 1) / (16 * CT);
     a.n_cg = (n_ct + kWavesPerBlock - 1) / kWavesPerBlock;
     a.flush_steps = kMfmaFlushSteps;
-    if constexpr (sizeof(T) == 8) {
-        // the counters live in the transform workspace, which nothing uses before the t-transform
-        MfmaQueue q;
-        q.next = static_cast<unsigned *>(ws.g);
-        q.done = q.next + 1;
-        q.n_ct = n_ct;
-        int chunks = 1;
-        for (int c0 = 0; c0 < g.nc; c0 += 16 * CT) chunks = std::max(chunks, mfma_tile_chunks(g, c0, 16 * CT));
-        const long lines = static_cast<long>(g.nk) * g.nc, n = lines * batch;
-        // one call's chunks apart where they fit beside the workspace: no chain
-        // of ordered additions (32x64 lines: 0.17 -> 0.09 ms)
-        q.slabs = chunks > 1 && slabs.p && static_cast<size_t>(chunks) * n * sizeof(double2) <= slabs.n
-                      ? static_cast<double2 *>(slabs.p) : nullptr;
-        // realizations of one launch: its items are counted in 32 bits
-        const int per = mfma_queue_batch(static_cast<long>(a.n_rg) * n_ct * chunks);
-        for (int b0 = 0; b0 < batch; b0 += per) {
-            a.batch = std::min(per, batch - b0);
-            a.zrow = static_cast<const double2 *>(ws.zrow) + b0 * lines;
-            a.zcol = static_cast<const double *>(ws.zcol) + b0 * ALayout<double>::NS * static_cast<long>(g.ncw) * g.nkp;
-            a.tout = static_cast<double2 *>(ws.tsum) + b0 * lines;
-            q.tiles = a.batch * a.n_rg * n_ct;
-            q.n_items = q.tiles * chunks;
-            const hipError_t e = launch_fill_u32(q.next, 1 + static_cast<size_t>(q.tiles), 0u, st);
-            if (e != hipSuccess) return e;
-            const int blocks = std::min((q.n_items + kWavesPerBlock - 1) / kWavesPerBlock, 3 * 256);
-            pairsum_mfma_queue_kernel<RT, CT><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a, q);
-        }
-        if (q.slabs)   // (one launch: they hold the whole call)
-            sum_slabs_kernel<<<dim3(static_cast<unsigned>((n + 255) / 256)), 256, 0, st>>>(
-                q.slabs, g, batch, 16 * CT, static_cast<double2 *>(ws.tsum));
-        return hipGetLastError();
-    } else {
     const long work = static_cast<long>(a.n_rg) * batch * a.n_cg;
     a.per_xcd = batch >= kNumXcd ? static_cast<int>((work + kNumXcd - 1) / kNumXcd) : 0;
     const long blocks = a.per_xcd > 0 ? static_cast<long>(a.per_xcd) * kNumXcd : work;
@@ -2302,11 +1949,10 @@ static hipError_t pairsum_mfma_t(const Geometry &g, const void *wtab, int batch,
     // launch (256x1024 x 64 and 512x8192 x 16: 1.2-1.4 % faster) and costs
     // small launches (the bridge example's 4 blocks per CU: 10 % slower)
     if (blocks >= kMfmaPrioBlocks)
-        pairsum_mfma_kernel<T, RT, CT, true><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a);
+        pairsum_mfma_kernel<RT, CT, true><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a);
     else
-        pairsum_mfma_kernel<T, RT, CT, false><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a);
+        pairsum_mfma_kernel<RT, CT, false><<<dim3(static_cast<unsigned>(blocks)), 64 * kWavesPerBlock, 0, st>>>(a);
     return hipGetLastError();
-    }
 }
 
 // Tile shapes of the matrix-core pair sum: 16 x 16 MFMA tiles per wave,
@@ -2319,28 +1965,13 @@ MfmaShape mfma_shape(int precision, int id)
     return precision == SRM3_FP64 ? f64[id] : f32[id];
 }
 
-size_t mfma_slab_bytes(const Geometry &g, int batch)
+hipError_t launch_pairsum_mfma(const Geometry &g, int shape, const void *wtab, int batch, const Workspace &ws,
+                               hipStream_t st)
 {
-    const int cols = 16 * mfma_shape(SRM3_FP64, 0).ct;
-    int chunks = 1;
-    for (int c0 = 0; c0 < g.nc; c0 += cols) chunks = std::max(chunks, mfma_tile_chunks(g, c0, cols));
-    return static_cast<size_t>(chunks) * batch * g.nk * g.nc * sizeof(double2);
-}
-
-hipError_t launch_pairsum_mfma(const Geometry &g, int precision, int shape, const void *wtab, int batch,
-                               const Workspace &ws, const Slabs &slabs, hipStream_t st)
-{
-    if (precision == SRM3_FP64) {
-        switch (shape) {
-        case 1: return pairsum_mfma_t<double, 2, 1>(g, wtab, batch, ws, slabs, st);
-        case 2: return pairsum_mfma_t<double, 1, 2>(g, wtab, batch, ws, slabs, st);
-        default: return pairsum_mfma_t<double, 2, 2>(g, wtab, batch, ws, slabs, st);
-        }
-    }
     switch (shape) {
-    case 1: return pairsum_mfma_t<float, 2, 1>(g, wtab, batch, ws, slabs, st);
-    case 2: return pairsum_mfma_t<float, 1, 2>(g, wtab, batch, ws, slabs, st);
-    default: return pairsum_mfma_t<float, 2, 2>(g, wtab, batch, ws, slabs, st);
+    case 1: return pairsum_mfma_t<2, 1>(g, wtab, batch, ws, st);
+    case 2: return pairsum_mfma_t<1, 2>(g, wtab, batch, ws, st);
+    default: return pairsum_mfma_t<2, 2>(g, wtab, batch, ws, st);
     }
 }
 
@@ -2382,7 +2013,7 @@ hipError_t launch_pairsum_hash(const Geometry &g, int precision, uint64_t key, d
                                   : pairsum_hash_t<float>(g, key, scale, batch, ws, sig, st);
 }
 
-template <typename T, int RT, int CT>
+template <int RT, int CT>
 static hipError_t persistent_mfma_t(const void *reqs, const void *items, const int *q_begin, int *q_next,
                                     int nblocks, hipStream_t st)
 {
@@ -2395,7 +2026,7 @@ static hipError_t persistent_mfma_t(const void *reqs, const void *items, const i
     a.q_begin = q_begin;
     a.q_next = q_next;
     a.flush_terms = kFlushTerms;
-    pairsum_persistent_mfma<T, RT, CT><<<dim3(static_cast<unsigned>(nblocks)), 64 * kWavesPerBlock, 0, st>>>(a);
+    pairsum_persistent_mfma<RT, CT><<<dim3(static_cast<unsigned>(nblocks)), 64 * kWavesPerBlock, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -2420,17 +2051,10 @@ hipError_t launch_pairsum_persistent(int precision, int R, const void *reqs, con
                                      int *q_next, int nblocks, hipStream_t st, bool mfma, int shape)
 {
     if (mfma) {
-        if (precision == SRM3_FP64) {
-            switch (shape) {
-            case 1: return persistent_mfma_t<double, 2, 1>(reqs, items, q_begin, q_next, nblocks, st);
-            case 2: return persistent_mfma_t<double, 1, 2>(reqs, items, q_begin, q_next, nblocks, st);
-            default: return persistent_mfma_t<double, 2, 2>(reqs, items, q_begin, q_next, nblocks, st);
-            }
-        }
         switch (shape) {
-        case 1: return persistent_mfma_t<float, 2, 1>(reqs, items, q_begin, q_next, nblocks, st);
-        case 2: return persistent_mfma_t<float, 1, 2>(reqs, items, q_begin, q_next, nblocks, st);
-        default: return persistent_mfma_t<float, 2, 2>(reqs, items, q_begin, q_next, nblocks, st);
+        case 1: return persistent_mfma_t<2, 1>(reqs, items, q_begin, q_next, nblocks, st);
+        case 2: return persistent_mfma_t<1, 2>(reqs, items, q_begin, q_next, nblocks, st);
+        default: return persistent_mfma_t<2, 2>(reqs, items, q_begin, q_next, nblocks, st);
         }
     }
     if (precision == SRM3_FP64) {

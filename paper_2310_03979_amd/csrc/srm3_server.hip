@@ -43,7 +43,8 @@ struct SlotHeader {
 struct Item {
     int kb, cg;
     double cost;
-    int chunks = 1;   // work items of the launch that it stands for (tiles of the split launch)
+    int chunks = 1;   // of a tile of the split or FP64 launch (0: run whole)
+    int items() const { return std::max(1, chunks); }   // work items of the launch that it stands for
 };
 
 struct SReq {
@@ -311,7 +312,11 @@ srm3_status srm3_server_submit(srm3_server_t s, const srm3_request *req, const s
         return fail(SRM3_E_NOMEM, "request needs %zu bytes, more than the server's budget %zu", q->bytes, s->arena.size);
     if (q->mode == 0) q->form = direct_form(r.plan, s->mfma ? s->mfma_shape : 0);
     if (q->mode == 0 && q->form == DirectForm::split) {
-        for (const SplitTile &t : split_tiles(q->g, 0))
+        for (const WorkTile &t : split_tiles(q->g, 0))
+            q->items.push_back({t.rs, t.cg, t.cost / (64.0 * waves_per_block() * s->R), t.chunks});
+        for (const Item &it : q->items) q->left += it.cost;
+    } else if (q->mode == 0 && q->form == DirectForm::mfma && s->cfg.precision == SRM3_FP64) {
+        for (const WorkTile &t : f64_tiles(q->g, s->mfma ? s->mfma_shape : 0, 0))
             q->items.push_back({t.rs, t.cg, t.cost / (64.0 * waves_per_block() * s->R), t.chunks});
         for (const Item &it : q->items) q->left += it.cost;
     } else if (q->mode == 0) {
@@ -387,7 +392,7 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         int n_items = 0;
         // (room: the next of a request's items still fits the step's list)
         auto full = [&]() { return spent >= budget && n_items >= min_items; };
-        auto room = [&](const SReq *q) { return n_items + q->items[q->cursor].chunks <= s->max_items; };
+        auto room = [&](const SReq *q) { return n_items + q->items[q->cursor].items() <= s->max_items; };
         if (s->cfg.policy == SRM3_SERVE_SHORTEST_FIRST) {
             std::vector<size_t> pri(s->order.size());
             for (size_t i = 0; i < pri.size(); ++i) pri[i] = i;
@@ -399,7 +404,7 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
                     take[i].push_back(q->items[q->cursor++]);
                     spent += take[i].back().cost;
                     q->left -= take[i].back().cost;
-                    n_items += take[i].back().chunks;
+                    n_items += take[i].back().items();
                 }
                 if (full()) break;
             }
@@ -413,7 +418,7 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
                     take[i].push_back(q->items[q->cursor++]);
                     spent += take[i].back().cost;
                     q->left -= take[i].back().cost;
-                    n_items += take[i].back().chunks;
+                    n_items += take[i].back().items();
                     more = true;
                 }
             }
@@ -430,18 +435,19 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         std::memcpy(P + s->off_req, s->preq.data(), s->preq.size());
         int *qb = reinterpret_cast<int *>(P + s->off_q);
         const size_t ib = persistent_item_bytes();
-        SplitList split;
+        WorkList split;
         int k = 0, k0[3] = {0, 0, 0};   // items of the vector list, then of the matrix-core list
         for (int kind = 0; kind < 2; ++kind) {
             const DirectForm form = kind == 0 ? DirectForm::vector : DirectForm::mfma;
+            const bool mine = kind == 0 || s->cfg.precision == SRM3_FP32;   // (FP64 matrix-core items: see below)
             double total = 0.0, acc = 0.0;
             for (size_t i = 0; i < take.size(); ++i)
-                if (s->order[i]->form == form)
+                if (mine && s->order[i]->form == form)
                     for (const Item &it : take[i]) total += it.cost;
             int *b = qb + kind * (kXcds + 1), q_ix = 1;
             b[0] = 0;
             for (size_t i = 0; i < take.size(); ++i) {
-                if (s->order[i]->form != form) continue;
+                if (!mine || s->order[i]->form != form) continue;
                 for (const Item &it : take[i]) {
                     while (q_ix < kXcds && acc >= total * q_ix / kXcds) b[q_ix++] = k - k0[kind];
                     fill_persistent_item(P + s->off_items + ib * k, s->order[i]->slot, it.kb, it.cg);
@@ -454,12 +460,13 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         }
         for (size_t i = 0; i < take.size(); ++i) {
             const SReq *q = s->order[i];
-            if (q->form != DirectForm::split) continue;
-            std::vector<SplitTile> tiles;
+            const bool f64 = q->form == DirectForm::mfma && s->cfg.precision == SRM3_FP64;
+            if (q->form != DirectForm::split && !f64) continue;
+            std::vector<WorkTile> tiles;
             for (const Item &it : take[i]) tiles.push_back({q->slot, it.kb, it.cg, it.chunks, it.cost});
-            split.add(split_shape(q->g), tiles);
+            split.add(f64 ? 0 : split_shape(q->g), tiles);
         }
-        SplitItems split_n;
+        WorkItems split_n;
         const std::vector<unsigned char> sitems = split.items(&split_n);
         const size_t off_split = s->off_items + ib * static_cast<size_t>(k);
         if (!sitems.empty()) std::memcpy(P + off_split, sitems.data(), sitems.size());
@@ -505,9 +512,12 @@ srm3_status srm3_server_step(srm3_server_t s, srm3_server_state *state)
         // ---- pair sums ----
         if (split.tiles() > 0) {
             char *D = static_cast<char *>(s->dev_stage[c].p);
-            e = launch_pairsum_split_items(D + s->off_req, D + off_split, split_n, split.tiles(),
-                                           static_cast<unsigned *>(s->split_ctr[c].p), st);
-            if (e != hipSuccess) return dev_err(e, "split-precision pair-sum kernel");
+            unsigned *ctr = static_cast<unsigned *>(s->split_ctr[c].p);
+            e = s->cfg.precision == SRM3_FP64
+                    ? launch_pairsum_f64_items(s->mfma ? s->mfma_shape : 0, D + s->off_req, D + off_split, split_n.begin[1],
+                                               split.tiles(), ctr, st)
+                    : launch_pairsum_split_items(D + s->off_req, D + off_split, split_n, split.tiles(), ctr, st);
+            if (e != hipSuccess) return dev_err(e, "split-precision or FP64 pair-sum kernel");
         }
         for (int kind = 0; kind < 2; ++kind) {
             if (k0[kind + 1] == k0[kind]) continue;

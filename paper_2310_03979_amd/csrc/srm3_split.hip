@@ -604,7 +604,7 @@ template <int NV>
 hipError_t launch_split_t(const SplitArgs &a, hipStream_t st)
 {
     // one block per CU (LDS)
-    const int blocks = std::min(a.n_items, 256);
+    const int blocks = std::min(a.n_items, kCus);
     pairsum_split_kernel<NV><<<dim3(static_cast<unsigned>(blocks)), 512, SplitShape<NV>::LDS, st>>>(a);
     return hipGetLastError();
 }
@@ -673,7 +673,7 @@ hipError_t launch_pairsum_split(const Geometry &g, const void *wtab, int batch, 
     return launch_split(split_nv(g.nk), a, st);
 }
 
-hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const SplitItems &n, int tiles,
+hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const WorkItems &n, int tiles,
                                       unsigned *counters, hipStream_t st)
 {
     hipError_t e = launch_fill_u32(counters, split_counter_words(tiles), 0u, st);
@@ -691,10 +691,10 @@ hipError_t launch_pairsum_split_items(const void *reqs, const void *items, const
 
 int split_shape(const Geometry &g) { return split_nv(g.nk) == 8 ? 0 : (split_nv(g.nk) == 4 ? 1 : 2); }
 
-std::vector<SplitTile> split_tiles(const Geometry &g, int req)
+std::vector<WorkTile> split_tiles(const Geometry &g, int req)
 {
     const int rsize = 32 * split_nv(g.nk), cb = split_cols(g.nk);
-    std::vector<SplitTile> v;
+    std::vector<WorkTile> v;
     for (int rs = 0; rs < split_row_tiles(g); ++rs) {
         const double r0 = static_cast<double>(rs) * rsize, r1 = std::min<double>(g.nk, r0 + rsize);
         for (int cg = 0; cg < split_col_tiles(g); ++cg) {
@@ -704,21 +704,19 @@ std::vector<SplitTile> split_tiles(const Geometry &g, int req)
             v.push_back({req, rs, cg, split_chunks(g, cb, cg), terms});
         }
     }
-    std::stable_sort(v.begin(), v.end(), [](const SplitTile &a, const SplitTile &b) { return a.cost > b.cost; });
+    std::stable_sort(v.begin(), v.end(), [](const WorkTile &a, const WorkTile &b) { return a.cost > b.cost; });
     return v;
 }
 
-void SplitList::add(int shape, const std::vector<SplitTile> &tiles)
+void WorkList::add(int shape, const std::vector<WorkTile> &tiles)
 {
     double c = 0.0;
-    for (const SplitTile &t : tiles) c += t.cost;
+    for (const WorkTile &t : tiles) c += t.cost;
     if (!tiles.empty()) runs_[shape].push_back({tiles, c});
     n_tiles_ += static_cast<int>(tiles.size());
 }
 
-void SplitList::add(int req, const Geometry &g) { add(split_shape(g), split_tiles(g, req)); }
-
-std::vector<unsigned char> SplitList::items(SplitItems *n)
+std::vector<unsigned char> WorkList::items(WorkItems *n)
 {
     std::vector<PItem> out;
     int tile0 = 0;
@@ -726,12 +724,14 @@ std::vector<unsigned char> SplitList::items(SplitItems *n)
         n->begin[i] = static_cast<int>(out.size());
         std::stable_sort(runs_[i].begin(), runs_[i].end(), [](const Run &a, const Run &b) { return a.cost > b.cost; });
         for (const Run &r : runs_[i]) {
-            int chunks = 0;
-            for (const SplitTile &t : r.tiles) chunks = std::max(chunks, t.chunks);
+            int chunks = 1;
+            for (const WorkTile &t : r.tiles) chunks = std::max(chunks, t.items());
             for (int c = 0; c < chunks; ++c)
                 for (size_t k = 0; k < r.tiles.size(); ++k) {
-                    const SplitTile &t = r.tiles[k];
-                    if (c < t.chunks) out.push_back({t.req, t.rs | (c << 16), t.cg, tile0 + static_cast<int>(k)});
+                    const WorkTile &t = r.tiles[k];
+                    const int chunk = t.chunks == 0 ? kTileWhole : c;
+                    if (c < t.items())
+                        out.push_back({t.req, t.rs | static_cast<int>(static_cast<unsigned>(chunk) << 16), t.cg, tile0 + static_cast<int>(k)});
                 }
             tile0 += static_cast<int>(r.tiles.size());
         }

@@ -59,7 +59,8 @@ static void split()
 
 // Work items of the FP64 matrix-core pair sum are counted in 32 bits: at the
 // largest grids and batches the library takes (2^31 lines a call, 65535
-// realizations), with 32 x 32 outputs a tile and chunks of 8 or 32 partners.
+// realizations), with tiles of 32 x 32 outputs and less, in chunks of at least
+// 16 partners.
 static void queue()
 {
     for (long nk : {1L, 2L, 3L, 16L, 100L, 4096L})
@@ -67,7 +68,7 @@ static void queue()
             for (long rows : {32L, 16L})
                 for (long cols : {32L, 16L}) {
                     const long tiles = ((nk + rows - 1) / rows) * ((nc + cols - 1) / cols);
-                    const long chunks = nc / (nk * nc <= 16384 ? 8 : 32) + 1;
+                    const long chunks = nc / 16 + 1;
                     const long batch = (1L << 31) / (nk * nc) < 65535 ? (1L << 31) / (nk * nc) : 65535;
                     const long per = mfma_queue_batch(tiles * chunks);
                     CHECK(per >= 1 && (per < batch ? per : batch) * tiles * chunks < (1L << 31) - 4096,
