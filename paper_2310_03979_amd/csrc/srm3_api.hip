@@ -1422,6 +1422,10 @@ std::string batch_signature(srm3_batch_t b)
     for (auto &gr : b->groups) {
         std::ostringstream k;
         k << gr.plan->g.nk << 'x' << gr.plan->g.nw << 'w' << gr.plan->g.W;
+        if (gr.mode == 0) {   // the form with the default tile: what the choice is between depends on it
+            const DirectForm f = direct_form(gr.plan, 0);
+            k << (f == DirectForm::split ? "/split" : f == DirectForm::mfma ? "/mfma" : "/vector");
+        }
         count[k.str()] += static_cast<int>(gr.members.size());
     }
     std::ostringstream o;
@@ -1560,12 +1564,15 @@ srm3_status srm3_batch_create(const srm3_request *reqs, int32_t n, int32_t flags
 
 // Time the candidate tile shapes on a stride sample of the batch (requests
 // sorted by cost) and keep the fastest; the choice is cached by signature.
-// Vector-ALU batches: rows per wave {R_max, R_max / 2} x workgroups per CU
-// {1, 2, 3, 4}.  Matrix-core batches: the tile shapes (32 x 32, 32 x 16 and
-// 16 x 32 outputs per wave) x workgroups per CU {2, 3, 4, 5} (the smaller
-// tiles leave room for more resident waves).
+// Only what a launch of the batch uses is varied.  Vector-ALU groups: rows per
+// wave {R_max, R_max / 2} x workgroups per CU {1, 2, 3, 4}.  Matrix-core groups:
+// the tile shapes (32 x 32, 32 x 16 and 16 x 32 outputs per wave), and in FP32
+// workgroups per CU {2, 3, 4, 5} (the smaller tiles leave room for more resident
+// waves).  Split-FP16 groups have one form and no parameter.
 static srm3_status batch_autotune(srm3_batch_t b, hipStream_t st)
 {
+    const bool vector = b->queue[0].n > 0, mfma32 = b->queue[1].n > 0, mfma64 = b->mfma && b->f64_tiles > 0;
+    if (!vector && !mfma32 && !mfma64) return SRM3_OK;
     const std::string sig = batch_signature(b);
     int R = b->R, bpc = b->blocks_per_cu, shape = b->mfma_shape;
     if (tune_lookup(sig, &R, &bpc, &shape)) {
@@ -1623,7 +1630,9 @@ static srm3_status batch_autotune(srm3_batch_t b, hipStream_t st)
         return SRM3_OK;
     };
     s = trial(Rmax, 0, defC);   // the default first
-    if (t->mfma) {
+    if (mfma64) {
+        for (int m = 1; m < kMfmaShapes && !s; ++m) s = trial(Rmax, m, defC);
+    } else if (mfma32) {
         for (int m = 0; m < kMfmaShapes && !s; ++m)
             for (int c : {2, 3, 4, 5})
                 if (!(m == 0 && c == defC) && (s = trial(Rmax, m, c))) break;
