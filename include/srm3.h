@@ -255,7 +255,8 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *   SRM3_ALGO_DIRECT     enumerates the unordered pairs of every line (the
  *                        coefficient sum of Section 4.1 / 4.3 as written), on
  *                        the vector ALUs, or in FP64 with n_kappa >= 16 on the
- *                        matrix cores, or in FP32 with n_kappa >= 32, partner
+ *                        matrix cores, or in FP32 with n_kappa >= 32 and
+ *                        (n_kappa - 16)^2 (2 support_w - 1) >= 12000, partner
  *                        factors (line_r, wind, product) of magnitude 0 or
  *                        1/64 .. 32 and pair weights whose largest magnitude
  *                        is 0 or 2^-64 .. 2^64 in split FP16 on the matrix
@@ -282,7 +283,8 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *                        phase rows with a block of weighted phases, evaluated
  *                        with 16x16x4 MFMAs (FP32: v_mfma_f32_16x16x4_f32 with
  *                        two-sum flushes; FP64: v_mfma_f64_16x16x4_f64).  FP32
- *                        plans with the default tile shape, n_kappa >= 32 and
+ *                        plans with the default tile shape, n_kappa >= 32,
+ *                        (n_kappa - 16)^2 (2 support_w - 1) >= 26000 and
  *                        factors and weights of moderate range (as above) take
  *                        each FP32 product as three FP16 products of split
  *                        phases with FP32 sums, as accurate as the FP32 form

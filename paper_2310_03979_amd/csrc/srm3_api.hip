@@ -107,16 +107,30 @@ srm3_status refresh_amp_table(srm3_plan_t p, hipStream_t st)
 }
 
 // Kernel of a plan's direct-form pair sum (shape: the matrix-core tile shape).
-// FP32 runs in split FP16 where the phase factors (with their line factors)
-// have magnitudes that two FP16 parts hold: as the default algorithm, and as
+//
+// FP32 runs in split FP16 where the phase factors (with their line factors) and
+// weights have magnitudes that it holds: as the default algorithm, and as
 // SRM3_ALGO_MFMA with the default tile shape (another shape asks for the FP32
-// MFMAs).  200x900 lines, 16 realizations: 44.2 ms on the vector ALUs, 10.4 so.
-// FP64 takes the FP64 MFMAs from 16 rows on (half a tile): 32x64 lines, one
-// realization, 0.32 ms on the vector ALUs, 0.09 so; 123x777, six: 11.5, 4.2.
+// MFMAs).  200x900 lines, 16 realizations: 44.2 ms on the vector ALUs, 9.8 so.
+// Not the smallest grids: its tiles have at least 64 rows and a step of all
+// eight waves per partner column.  The lines in (rows - 16)^2 x partner columns
+// are where the two sides cross in calls of 1, 16 and 256 realizations: against
+// the vector ALUs 48x6 lines (11264) 0.044 and 0.045 ms, 32x24 (12032) 0.093 and
+// 0.084, 64x6 (25344) 0.052 and 0.046; against the FP32 MFMAs 32x32 (16128) 0.098
+// and 0.102, 64x6 0.0446 and 0.0455, 48x17 (33792) 0.081 and 0.078, 32x64 (32512)
+// 0.166 and 0.127.
+//
+// FP64 takes the FP64 MFMAs from 16 rows on, one row tile: 16x333 lines, 8
+// realizations, 0.76 ms on the vector ALUs, 0.14 so; 64 realizations 0.96, 0.53.
+// With fewer rows part of each product is idle: 8x333, 512 realizations, 1.6 and
+// 1.9 ms (small calls gain there too, 12x333 x 8 0.76 and 0.14: SRM3_ALGO_MFMA).
 DirectForm direct_form(srm3_plan_t p, int shape)
 {
     if (p->algo == SRM3_ALGO_MFMA && shape != 0) return DirectForm::mfma;
-    if (p->split_range && split_supported(p->g, p->precision)) return DirectForm::split;
+    const double r = p->g.nk - 16.0, work = r * r * p->g.ncw;
+    if (p->split_range && split_supported(p->g, p->precision) &&
+        work >= (p->algo == SRM3_ALGO_MFMA ? kSplitWorkMfma : kSplitWorkVector))
+        return DirectForm::split;
     if (p->algo == SRM3_ALGO_MFMA || (p->precision == SRM3_FP64 && p->g.nk >= 16)) return DirectForm::mfma;
     return DirectForm::vector;
 }

@@ -183,6 +183,7 @@ constexpr double kSplitMaxFactor = 32.0, kSplitMinFactor = 1.0 / 64;
 // holds W 2^-10 and T 2^10, which must neither overflow nor lose bits below
 // FP32's normal numbers.
 constexpr double kSplitMaxWeight = 1.8446744073709552e19, kSplitMinWeight = 5.421010862427522e-20;   // 2^64, 2^-64
+constexpr double kSplitWorkVector = 12000.0, kSplitWorkMfma = 26000.0;   // see direct_form
 constexpr int kSplitMinRows = 32;   // (the FP16 parts fit the a operand region from 30 rows on)
 // Its operand of one realization: [2W - 1 columns][re hi, re lo, im hi, im lo]
 // [8 + nk8] FP16, kappa-contiguous: eight zeros (rows -8 .. -1), then nk8 =

@@ -46,3 +46,33 @@ def test_weights_near_the_ends_of_fp32(lib, oracle_mod, algorithm, weight, line_
     ref = P.coefficients(seed=5)
     assert np.isfinite(C).all()
     assert np.linalg.norm(C - ref) <= TOL * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("nk,nw,same", [(32, 23, False),   # vector ALUs and FP32 MFMAs
+                                        (32, 24, False),   # split and FP32 MFMAs
+                                        (32, 50, False),
+                                        (32, 52, True),    # split both
+                                        (64, 6, False), (100, 3, True)])
+def test_small_grids_at_the_lines_between_the_forms(lib, oracle_mod, nk, nw, same):
+    """The smallest grids stay with the FP32 forms (the default algorithm's line
+    lies below that of the matrix cores'): against the oracle on both sides, the
+    form told by the bits of the two algorithms."""
+    import torch
+    wl = inp.small_grid(nk, nw, batch=2, seed_base=9)
+    print(f"[gpu] split lines {nk}x{nw}", flush=True)
+    b2 = inp.random_b2_dense(nw, 9, scale=0.3)
+    beta = inp.random_beta_table(nw, 10)
+    bis = dict(kind="dense", b2=b2, beta=beta, beta_mode="table", support_w=nw, cap=wl.cap)
+    P = oracle_mod.Problem(nk, nw, nw, wl.d_kappa, wl.d_omega, wl.spectrum(), b2, beta, wl.cap)
+    ref = P.coefficients(seed=int(wl.seeds()[1]))
+    C = {}
+    for algorithm in ("direct", "mfma"):
+        plan = lib.srm3_plan(wl.grid_dict(), wl.spectrum(), bis, "fp32")
+        lib.srm3_plan_set_algorithm(plan, algorithm)
+        c = torch.empty((2,) + plan.coeff_shape, dtype=torch.complex64, device="cuda")
+        lib.srm3_coefficients(plan, wl.seeds(), c)
+        torch.cuda.synchronize()
+        C[algorithm] = c
+        got = c[1].cpu().numpy().astype(np.complex128)
+        assert np.linalg.norm(got - ref) <= TOL * np.linalg.norm(ref), algorithm
+    assert torch.equal(C["direct"], C["mfma"]) is same

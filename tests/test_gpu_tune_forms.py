@@ -22,10 +22,10 @@ def lib():
 
 def _batch(lib, nk, precision, line_r=None, algorithm="mfma"):
     import torch
-    wl = inp.small_grid(nk, 40)
-    bis = dict(kind="dense", b2=inp.random_b2_dense(40, 4, scale=0.2), beta_mode="seeded", beta_seed=11, support_w=40, cap=0.9)
+    wl = inp.small_grid(nk, 50)
+    bis = dict(kind="dense", b2=inp.random_b2_dense(50, 4, scale=0.2), beta_mode="seeded", beta_seed=11, support_w=50, cap=0.9)
     if line_r is not None:
-        bis["line_r"] = np.full((nk, 79), line_r)
+        bis["line_r"] = np.full((nk, 99), line_r)
     plan = lib.srm3_plan(wl.grid_dict(), wl.spectrum(), bis, precision)
     lib.srm3_plan_set_algorithm(plan, algorithm)
     reqs = [dict(plan=plan, seed=7 + i, out=torch.empty(plan.field_shape, dtype=plan.real_dtype, device="cuda"))
@@ -39,7 +39,7 @@ def test_choices_of_another_form_are_not_taken(lib, tmp_path, monkeypatch):
     monkeypatch.setenv("SRM3_TUNE_CACHE", str(path))
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     # as an earlier library wrote it: the same grids, a tile of 32 x 16
-    old = "".join(f"fp32;mfma;cu{cus};{nk}x40w40*3 8 3 1\n" for nk in (34, 24))
+    old = "".join(f"fp32;mfma;cu{cus};{nk}x50w50*3 8 3 1\n" for nk in (34, 24))
     path.write_text(old)
     print("[gpu] tune forms", flush=True)
     split = _batch(lib, 34, "fp32")
@@ -48,7 +48,7 @@ def test_choices_of_another_form_are_not_taken(lib, tmp_path, monkeypatch):
     mfma = _batch(lib, 34, "fp32", line_r=100.0)       # factors off the split form: tuned, under a signature of its own
     mfma.run()
     lines = path.read_text().splitlines()
-    assert len(lines) == 3 and "/mfma" in lines[2] and lines[2].startswith(f"fp32;mfma;cu{cus};34x40w40/mfma*3 ")
+    assert len(lines) == 3 and "/mfma" in lines[2] and lines[2].startswith(f"fp32;mfma;cu{cus};34x50w50/mfma*3 ")
     # its choice, had it been another tile, stays its own
     path.write_text(old + lines[2].rsplit(" ", 1)[0] + " 1\n")
     again, split = _batch(lib, 34, "fp32", line_r=100.0), _batch(lib, 34, "fp32")
