@@ -48,8 +48,9 @@ SPLIT_MIN_ROWS = 32             # n_kappa from which FP32 plans with the default
 
 
 def split_form(n_kappa, shape=0):
-    """Whether an FP32 pair sum runs the split-FP16 form (both the default
-    algorithm and the matrix cores'; smaller grids and explicit tiles don't)."""
+    """Whether an FP32 pair sum of a workload here runs the split-FP16 form (both
+    the default algorithm and the matrix cores'; grids of fewer rows and explicit
+    tiles don't, nor the smallest grids, of which there is none here)."""
     return shape == 0 and n_kappa >= SPLIT_MIN_ROWS
 
 
@@ -1202,7 +1203,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"{wl.name}: {wl.n_kappa}x{wl.n_omega} lines, {wl.n_x}x{wl.n_t} field, "
                                f"batch {B}, bicoherence support {wl.support_w}",
-                   "global_batch": B, "precision": "fp32 fixed-point phases, compensated pair sums",
+                   "global_batch": B, "precision": ("fp32 fixed-point phases, "
+                                                    + ("pair sums in split FP16 products, FP32 sums on three levels" if split else
+                                                       "compensated pair sums")),
                    "pair_kernel": SPLIT_LABEL if split else "matrix cores (FP32 MFMA)" if mfma else "vector ALUs"},
         "roofline": roofline,
         "cpu_baseline": cpu,

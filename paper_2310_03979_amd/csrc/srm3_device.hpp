@@ -165,11 +165,18 @@ __device__ __forceinline__ void phase_line(uint32_t u, const double2 *ptab, cons
     }
 }
 
-// Ordered additions to a sum by several waves or blocks, counted: one waits
-// until n are counted, adds, and counts itself once its stores are done.  The
-// sums are read and written with agent-scope (coherent) accesses, so no cache
-// has to be written back or invalidated around them: with fences instead, one
-// addition in a launch of 3072 waves cost over 200 us.
+// Ordered additions to a sum by several blocks, counted: one waits until n are
+// counted, adds, and counts itself once its stores are done.  With fences around
+// them, one addition in a launch of 3072 waves cost over 200 us.  Without, the
+// order rests on three properties of gfx942 and gfx950 that the language does
+// not promise: every access to the sums and the counters has agent scope (sc1:
+// loads are not served from an XCD's own copy, stores are written through to
+// where the other XCDs read), so no cache holds a line to write back or
+// invalidate; s_waitcnt waits until a wave's stores have been acknowledged from
+// there, before any wave of the block passes the barrier and the count is
+// stored; and loads are issued in program order, those of the sums after the
+// load that returned the count.  The compiler is kept from moving them by empty
+// asm statements that clobber memory.
 __device__ __forceinline__ unsigned load_count(const unsigned *count)
 {
     return __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

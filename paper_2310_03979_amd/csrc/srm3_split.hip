@@ -146,11 +146,11 @@ __global__ __launch_bounds__(256) void phase_split_kernel(SeedChunk seeds, const
 // launch.  The wait ends: an item is taken only after all items before it were
 // taken by running blocks, and the first unfinished one waits for nothing.
 //
-// Bound by the chip's power with the matrix cores 70 % busy: at 256x1024
-// (batch 64) the pair sum takes 62 ms (FP32 16x16x4 MFMAs: 169 ms), of which
-// 35 ms would be MFMA issue at 2.4 GHz, and the clock falls to 2.03 GHz under
-// it (taking a quarter of the MFMAs out gains 18 %, a third of the LDS reads
-// 6 %, the weights 3 %).  512x8192 (support 2048, batch 16): 298 ms (817).
+// Bound by the chip's power: at 256x1024 (batch 64) the pair sum takes 60 ms
+// (FP32 16x16x4 MFMAs: 169 ms) with the matrix cores busy 72 % of the cycles at
+// 1.99 GHz (counters; 36 ms of MFMA issue at 2.4 GHz), at 512x8192 (support 2048,
+// batch 16) 295 ms (817), 75 % at 1.94.  Taking a quarter of the MFMAs out gains
+// 18 %, a third of the LDS reads 6 %, the weights 3 %.
 // Tried: 64 x 32 outputs per wave in passes of 128 rows (72 ms: a second pass
 // over the partner columns, spills); both operands of the next step in a
 // second register set (spills, 100 ms); 32x32x16 MFMAs (7 % slower).

@@ -33,12 +33,13 @@ struct YpairArgs {
 // (zero rows after the table, or pairs outside the support) and the last
 // partner's a operand.  Per term: t = a b (4 operations), acc += w t (4 FMAs).
 //
-// Bound by the vector ALUs (8 operations per term, 9.0 issued; 100 % busy at
-// 256x1024, where the clock falls to 2 GHz).  Buffer loads took the window's
-// address arithmetic away, scalar loads one of two LDS reads per term: 256x1024,
-// batch 64, FP32 16.7 -> 15.1 ms for the whole call, batch 8 in FP64 4.25 ->
-// 3.82; the process 4096x4096 6.69 -> 6.13.  Column tiles in the outer order (fewer passes over the weights, but every
-// wave's rows fall out of the scalar cache): 24 ms.
+// Bound by the vector ALUs (8 operations per term, 9.0 issued: busy all of the
+// cycles at 256x1024, where the clock falls to 2.1 GHz).  Buffer loads took the
+// window's address arithmetic away, scalar loads one of two LDS reads per term:
+// 256x1024, batch 64, FP32 16.1 -> 14.8 ms for the whole call (14.5 with the
+// column transforms that came after); the process of 4096 frequencies, 4096
+// realizations 6.3 -> 5.8.  Column tiles in the outer order (fewer passes over the
+// weights, but every wave's rows fall out of the scalar cache): 24 ms.
 constexpr int kY2Rows = 8;   // DFT rows per wave
 constexpr int kWaves = 4;    // per block
 
@@ -245,9 +246,12 @@ hipError_t launch_ypair(int precision, const Geometry &g, const KfftGeom &k, con
     y.one_sided = k.one_sided;
     if (precision == SRM3_FP64) return ypair_t<double, false>(y, st);
     // FP32: the scalar loads of a pay while the waves of a launch share its rows
-    // in the scalar cache: large kappa-DFTs (256x1024, batch 64: 15.1 ms, 15.7
-    // with a in LDS), not small ones (100x333, 3: 0.187, 0.162) nor the process,
-    // whose rows lie far apart (4096x4096: 6.68, 6.13; 1000x513: 0.318, 0.226).
+    // in the scalar cache, in large kappa-DFTs, not in small ones nor the process,
+    // whose rows lie far apart (scalar loads, LDS, in ms a call): 256x1024 lines
+    // with 2048 waves 0.47, 0.38, 8192 1.10, 1.00, 16384 1.92, 1.89, 131072 14.57,
+    // 14.70; 256x256 with 8192 0.362, 0.356, 16384 0.620, 0.634; 512x512 with 8192
+    // 0.605, 0.581, 16384 1.033, 1.043, 65536 4.01, 4.09; 32x2048 (M = 64) with
+    // 32768 7.39, 7.14; the process 4096x4096 6.45, 5.73, 1000x513 0.295, 0.191.
     // Both sum alike, bitwise.
     const long waves = static_cast<long>(y.batch) * ((y.M + kY2Rows - 1) / kY2Rows) * ((y.nca + 63) / 64);
     const bool scalar = !k.one_sided && waves >= 16384;
