@@ -7,17 +7,17 @@
 // has the same bits in every launch.  An item is a chunk, added to the tile's
 // sum in memory after the chunk before it (an ordered addition, about 10 us from
 // one block to the next); or a chunk whose sum goes to a slab of its own, the
-// slabs being added afterwards; or a whole tile.  Items are taken from a queue
-// in order, chunk by chunk over all tiles, so the first unfinished one waits
-// for nothing.
+// slabs being added afterwards; or a whole tile.  Items with ordered additions
+// are taken from a queue in order, chunk by chunk over all tiles, so the first
+// unfinished one waits for nothing; the others are the launch's blocks.
 //
 // Bound by the FP64 matrix cores where rows and realizations fill them (256x1024
 // lines, 64 realizations: 318 ms, 62 TFLOP/s in the three products of a pair
 // term) and by the chain of additions and its tail in small calls.
 // With a wave to a chunk instead, each chunk added to memory by its wave (four
 // times the additions; batches and the server ran whole tiles, one wave each):
-// that batch 328 ms, 32x64 lines x 64 0.31 ms (now 0.11), 16x333 x 8 1.07
-// (0.11), 24 mixed grids of 64x128 to 256x1024 in a batch 64 (20.5).
+// that batch 328 ms, 32x64 lines x 64 0.31 ms (now 0.10), 16x333 x 8 1.07
+// (0.10), 24 mixed grids of 64x128 to 256x1024 in a batch 64 (20.5).
 #include <algorithm>
 
 #include "srm3_mfma.hpp"
@@ -39,6 +39,7 @@ constexpr int kWholeWork = 160;   // see whole_tiles
 // the two: 32x128 with 128 0.091 (32: 0.056), 32x333 x 8 with 32 0.33 (128: 0.18).
 __host__ __device__ inline int f64_chunk_max(const Geometry &g)
 {
+    if (g.nk < 8) return 128;   // (a chunk of 32 is hardly longer than the meeting of its waves)
     if (g.nk * g.nc <= 16384) return g.ncw <= 256 ? 32 : 64;
     return g.nk < 64 ? 128 : 64;
 }
@@ -74,7 +75,7 @@ struct F64Args {
     int tiles;          // batch * n_rg * n_ct
     int n_items;        // tiles, or tiles * chunks of the widest
     int whole;          // an item is a whole tile
-    unsigned *queue;    // next item, zero at launch
+    unsigned *queue;    // next item, zero at launch; or null: item blockIdx.x (no additions in order)
     unsigned *done;     // chunks added per tile, zero at launch
     double2 *slabs;     // or null: [chunks][batch][nk][nc], each chunk's sums apart (added by sum_slabs_kernel)
     const PReq *reqs;   // with items: the requests and their work list
@@ -181,9 +182,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void p
     __shared__ int s_item[2];
     for (int turn = 0;; turn ^= 1) {
         // (two slots: a skipped item has no barrier between its read and the next write)
-        if (threadIdx.x == 0) s_item[turn] = static_cast<int>(atomicAdd(a.queue, 1u));
-        __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(s_item[turn]);
+        int item = static_cast<int>(blockIdx.x);
+        if (a.queue) {
+            if (threadIdx.x == 0) s_item[turn] = static_cast<int>(atomicAdd(a.queue, 1u));
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(s_item[turn]);
+        } else if (turn) {
+            return;
+        }
         if (item >= a.n_items) return;
         int rg, ct, chunk, tile;
         if (a.items) {
@@ -275,7 +281,7 @@ bool whole_tiles(const Geometry &g, const MfmaShape &m, long tiles)
 template <int RT, int CT>
 hipError_t launch_t(const F64Args &a, hipStream_t st)
 {
-    const int blocks = std::min(a.n_items, 3 * kCus);
+    const int blocks = a.queue ? std::min(a.n_items, 3 * kCus) : a.n_items;
     pairsum_f64_kernel<RT, CT><<<dim3(static_cast<unsigned>(blocks)), 64 * kWaves, 0, st>>>(a);
     return hipGetLastError();
 }
@@ -307,9 +313,6 @@ hipError_t launch_pairsum_f64(const Geometry &g, int shape, const void *wtab, in
     a.g = g;
     a.n_rg = (g.nk + 16 * m.rt - 1) / (16 * m.rt);
     a.n_ct = (g.nc + cols - 1) / cols;
-    // the counters live in the transform workspace, which nothing uses before the t-transform
-    a.queue = static_cast<unsigned *>(ws.g);
-    a.done = a.queue + 1;
     const int chunks = widest_chunks(g, cols);
     const bool slabs_fit = chunks > 1 && slabs.p && f64_slab_bytes(g, shape, batch) <= slabs.n;
     // (slabs where whole tiles would leave CUs idle: 8x64 lines, one realization,
@@ -327,7 +330,13 @@ hipError_t launch_pairsum_f64(const Geometry &g, int shape, const void *wtab, in
         a.tout = static_cast<double2 *>(ws.tsum) + b0 * lines;
         a.tiles = a.batch * a.n_rg * a.n_ct;
         a.n_items = a.whole ? a.tiles : a.tiles * chunks;
-        hipError_t e = launch_fill_u32(a.queue, 1 + (a.whole || a.slabs ? 0 : static_cast<size_t>(a.tiles)), 0u, st);
+        hipError_t e = hipSuccess;
+        if (!a.whole && !a.slabs) {
+            // the counters live in the transform workspace, which nothing uses before the t-transform
+            a.queue = static_cast<unsigned *>(ws.g);
+            a.done = a.queue + 1;
+            e = launch_fill_u32(a.queue, f64_counter_words(a.tiles), 0u, st);
+        }
         if (e == hipSuccess) e = launch_shape(shape, a, st);
         if (e != hipSuccess) return e;
     }
