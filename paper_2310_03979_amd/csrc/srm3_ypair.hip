@@ -160,8 +160,8 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
         T2 a0[2][R], w0[2], w1[2];
         w0[0] = load_w(0);
         w0[1] = load_w(1);
-        if constexpr (sizeof(T) == 4 && !ALDS) {
-            // a two steps ahead, in two register sets
+        if constexpr (!ALDS) {
+            // a two steps ahead, in two sets of scalar registers (FP32 only: see launch_ypair)
             T2 a1[2][R];
             load_a(a0, 0);
             for (int s = 0; s < C; s += 4) {
@@ -175,9 +175,7 @@ __global__ __launch_bounds__(64 * kWaves) void ypair2_kernel(YpairArgs a)
                 pair(a1, w1, s + 2);
             }
         } else {
-            // one set: two would not fit the scalar registers (or a is in LDS)
-            constexpr int UNROLL = ALDS ? 2 : 1;
-#pragma unroll UNROLL
+#pragma unroll 2
             for (int s = 0; s < C; s += 2) {
                 load_a(a0, s);
                 w1[0] = load_w(s + 2);
@@ -244,7 +242,12 @@ hipError_t launch_ypair(int precision, const Geometry &g, const KfftGeom &k, con
     y.kw0 = k.kw0;
     y.wh_rows = k.wh_rows;
     y.one_sided = k.one_sided;
-    if (precision == SRM3_FP64) return ypair_t<double, false>(y, st);
+    // FP64: a in LDS.  Scalar loads of it take the scalar registers of two steps,
+    // so they are not requested ahead: 256x1024 lines, one realization, 0.65 ms,
+    // LDS 0.49; eight 3.68, 3.06; 32x2048 x 4 1.22, 0.79; the process 4096x4096 11.9,
+    // 8.9 (both staged in LDS through registers of 64-bit addresses, before: 0.58,
+    // 3.85, 1.08, 11.0).
+    if (precision == SRM3_FP64) return ypair_t<double, true>(y, st);
     // FP32: the scalar loads of a pay while the waves of a launch share its rows
     // in the scalar cache, in large kappa-DFTs, not in small ones nor the process,
     // whose rows lie far apart (scalar loads, LDS, in ms a call): 256x1024 lines
