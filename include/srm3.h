@@ -287,7 +287,7 @@ srm3_status srm3_rows_per_wave(srm3_plan_t plan, int32_t *rows);
  *                        (n_kappa - 16)^2 (2 support_w - 1) >= 26000 and
  *                        factors and weights of moderate range (as above) take
  *                        each FP32 product as three FP16 products of split
- *                        phases with FP32 sums, as accurate as the FP32 form
+ *                        phases with FP32 sums, no less accurate than the FP32 form
  *                        (v_mfma_f32_16x16x32_f16).  Same
  *                        result up to rounding.  Output rows go in groups of
  *                        32 kappa rows: grids with few rows (a 1-D process has
