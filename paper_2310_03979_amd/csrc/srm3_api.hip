@@ -121,9 +121,9 @@ srm3_status refresh_amp_table(srm3_plan_t p, hipStream_t st)
 // 0.166 and 0.127.
 //
 // FP64 takes the FP64 MFMAs from 16 rows on, one row tile: 16x333 lines, 8
-// realizations, 0.76 ms on the vector ALUs, 0.14 so; 64 realizations 0.96, 0.53.
+// realizations, 0.76 ms on the vector ALUs, 0.10 so; 64 realizations 0.96, 0.47.
 // With fewer rows part of each product is idle: 8x333, 512 realizations, 1.6 and
-// 1.9 ms (small calls gain there too, 12x333 x 8 0.76 and 0.14: SRM3_ALGO_MFMA).
+// 1.9 ms (small calls gain there too, 12x333 x 8 0.76 and 0.09: SRM3_ALGO_MFMA).
 DirectForm direct_form(srm3_plan_t p, int shape)
 {
     if (p->algo == SRM3_ALGO_MFMA && shape != 0) return DirectForm::mfma;
